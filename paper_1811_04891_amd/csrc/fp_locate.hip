@@ -565,6 +565,7 @@ __global__ __launch_bounds__(kWave) void k_locate(LocArgs a, const double *__res
 }
 
 #include "fp_mfma.inc"
+#include "fp_start.inc"
 #include "fp_newton8.inc"
 #include "fp_mixed8.inc"
 #include "fp_newton_pl.inc"
