@@ -333,7 +333,9 @@ FP_API int fp_extrapolate(long long n, int order, const double *const *h_hist, d
  *     concurrently on their slots and release slot and workspace when their
  *     stream completes; waiting requests are then admitted.
  *   - Results equal those of findpts + findpts_eval on the request alone
- *     (every point's result depends only on that point and the mesh).
+ *     (every point's result depends only on that point, the mesh, and
+ *     whether the call has at most 16,384 points: such calls run other
+ *     kernels, whose results may differ by rounding).
  *   - Latency of a request = host time from fps_submit to the completion of
  *     its last kernel (a host callback on its stream).
  *

@@ -14,6 +14,7 @@
 #include "fp_group.h"
 #include "fp_internal.h"
 #include "fp_mfma.h"
+#include "fp_wave.h"
 
 namespace fp {
 
@@ -245,6 +246,7 @@ __global__ __launch_bounds__(kEvThreads) void k_eval_grp(EvArgs a, FieldPtrs F,
 // fragments of a field the launch does not have.
 constexpr int kUnitEvalMfma = 256;  // points of one element per work unit
 constexpr int kEvMfmaMaxN1 = 8;      // orders with the matrix-core kernel
+static_assert(kMixed32MaxN1 == kEvMfmaMaxN1, "binary32 interpolation is the matrix-core kernel's");
 // Smallest pass that takes the staged path: below it the grouping's launches
 // cost more than the scattered stores they avoid.
 constexpr int kEvStageMin = 1 << 18;
@@ -374,6 +376,71 @@ void k_eval_mfma(EvArgs a, FieldPtrs F,
     }
 }
 
+// Small calls: one wavefront per point, no grouping by element.  A small call
+// is bound by the grouping's launches (counters, scan, scatter) and by the few
+// wavefronts its work units fill, not by the element values that grouped
+// points would share; the lanes take the element's node rows, so a point costs
+// one read of them.
+template <int N1>
+__global__ __launch_bounds__(kWave) void k_eval_point(EvArgs a, FieldPtrs F,
+                                                      const double *__restrict__ basis)
+{
+    __shared__ double2 sh[48];
+    const BasisPtr<double> B{as_const(basis)};
+    WaveBasis<N1> W;
+    W.init(B, sh);
+    for (int p = blockIdx.x; p < a.npts; p += gridDim.x) {
+        const int e = a.el[p];
+        const bool ok = a.code[p] != FP_NOT_FOUND && e >= 0 && e < a.E;
+        double v[kMaxEvalFields];
+#pragma unroll
+        for (int f = 0; f < kMaxEvalFields; ++f) v[f] = 0.0;
+        if (ok) {
+            const double r[3] = {a.rst[3 * (long long)p], a.rst[3 * (long long)p + 1],
+                                 a.rst[3 * (long long)p + 2]};
+            W.basis(r);
+#pragma unroll
+            for (int f = 0; f < kMaxEvalFields; ++f)
+                if (f < a.nf) v[f] = W.field_part(F.f[f] + (long long)e * WaveShape<N1>::V);
+            wave_sum4(v[0], v[1], v[2], v[3]);
+            if (a.nf > 4) wave_sum4(v[4], v[5], v[6], v[7]);
+        }
+        if (W.lane == 0) {
+#pragma unroll
+            for (int f = 0; f < kMaxEvalFields; ++f)
+                if (f < a.nf) a.out[f * a.ostride + p] = ok ? v[f] : NAN;
+        }
+    }
+}
+
+static hipError_t launch_eval_point(int n1, const EvArgs &a, const FieldPtrs &F, const double *B,
+                                    hipStream_t s)
+{
+    const int nblk = a.npts < kPointMax ? a.npts : kPointMax;
+#define FP_EVAL_POINT(N1) \
+    case N1: k_eval_point<N1><<<nblk, kWave, 0, s>>>(a, F, B); break
+    switch (n1) {
+        FP_EVAL_POINT(2);
+        FP_EVAL_POINT(3);
+        FP_EVAL_POINT(4);
+        FP_EVAL_POINT(5);
+        FP_EVAL_POINT(6);
+        FP_EVAL_POINT(7);
+        FP_EVAL_POINT(8);
+        FP_EVAL_POINT(9);
+        FP_EVAL_POINT(10);
+        FP_EVAL_POINT(11);
+        FP_EVAL_POINT(12);
+        FP_EVAL_POINT(13);
+        FP_EVAL_POINT(14);
+        FP_EVAL_POINT(15);
+        FP_EVAL_POINT(16);
+        default: return hipErrorInvalidValue;
+    }
+#undef FP_EVAL_POINT
+    return hipGetLastError();
+}
+
 // Launches the order's interpolation kernel over the work units of n points.
 static hipError_t launch_eval_kernel(int n1, int E, int n, const EvArgs &a, const FieldPtrs &F,
                                      const double *B, const float *B32, bool mixed, hipStream_t s)
@@ -449,6 +516,7 @@ int run_eval(fp_handle *h, const Work &w, int npts, const int *code, const int *
              const double *rst, int nfields, const double *const *h_fields, double *out,
              hipStream_t s, bool timed)
 {
+    const bool small = small_call(h, npts);
     const size_t res_bytes = w.res ? (size_t)w.M * w.MC * 4 * sizeof(double) : 0;
     for (int start = 0; start < npts; start += w.M) {
         const int n = (npts - start < w.M) ? npts - start : w.M;
@@ -471,7 +539,7 @@ int run_eval(fp_handle *h, const Work &w, int npts, const int *code, const int *
         bool plan_ok = false;
         const GroupPlan gp = group_plan(n, h->E, &plan_ok);
         const int nf_max = nfields < kMaxEvalFields ? nfields : kMaxEvalFields;
-        const bool staged = h->n1 <= kEvMfmaMaxN1 && n >= kEvStageMin && plan_ok && w.ev_slot &&
+        const bool staged = !small && h->n1 <= kEvMfmaMaxN1 && n >= kEvStageMin && plan_ok && w.ev_slot &&
                             res_bytes >= group_transient_bytes(gp) &&
                             res_bytes >= (size_t)n * nf_max * sizeof(double);
         for (int f0 = 0; f0 < nfields; f0 += kMaxEvalFields) {
@@ -497,6 +565,11 @@ int run_eval(fp_handle *h, const Work &w, int npts, const int *code, const int *
             FieldPtrs F{};
             for (int f = 0; f < nf; ++f) F.f[f] = h_fields[f0 + f];
             const int pb = (n + 255) / 256;
+            if (small) {
+                if (timed && f0 == 0) FP_HIP(hipEventRecord(l0, s));
+                FP_HIP(launch_eval_point(h->n1, a, F, h->d_basis, s));
+                continue;
+            }
             if (f0 == 0) {
                 if (staged) {
                     GroupBufs gb;

@@ -16,6 +16,9 @@ constexpr int kMaxN1 = 16;       // N <= 15
 constexpr int kMaxEvalFields = 8; // fields per interpolation launch
 constexpr int kEvSink = 512;       // doubles in Work::ev_sink (a power of two)
 constexpr int kStats = 6;          // device counters of a handle (findpts_stats)
+constexpr int kPointMax = 16384;   // points of the largest call taken one wavefront per point
+constexpr int kMixed32MaxN1 = 8;   // orders whose mixed precision interpolates in binary32
+constexpr int kPointCounters = 5;  // counters of one wavefront of such a call
 constexpr int kTimedPhases = 5;    // timed phases (findpts_timing_read)
 constexpr int kWave = 64;
 constexpr int kXcds = 8;  // accelerator dies; workgroups are dealt to them in turn
@@ -91,6 +94,7 @@ struct Work {
     int *scan_tmp = nullptr;  // block sums of the device scans
     unsigned *cand_part = nullptr;  // ceil(M / 256): per-block candidate counts
     unsigned *iter_part = nullptr;  // unit_grid(E, M, kUnitMin): Newton iterations per block
+    unsigned *pt_part = nullptr;  // min(M, kPointMax) x kPointCounters (small calls)
     int *ev_cnt = nullptr;    // E + 1
     int *ev_off = nullptr;    // E + 1
     int *ev_pos = nullptr;    // M
@@ -306,6 +310,22 @@ std::vector<double> bernstein_to_nodal_inverse(int N, const double *z);
 
 // Fill n ints with a value (a kernel, so that it may be graph-captured).
 hipError_t fill_int(int *p, int value, long long n, hipStream_t s);
+
+// Calls taken one wavefront per point, in one kernel, instead of being grouped
+// by element (k_point, k_eval_point): decided by the call's size alone, so that
+// a call's results do not depend on how it is cut into passes.  The grouped
+// path costs a call of 1,000 points 92 to 238 us of findpts at orders 3 to 9
+// (about 20 launches and a chain of 16-slot rounds) against 30 to 52 us, and
+// 1.3 to 2.6 ms at orders 12 and 15 against 0.08 to 0.23; at kPointMax points
+// the two are level on meshes with a few points per element (order 3: 111
+// against 91 us; order 7: 173 against 116) and one wavefront per point still
+// takes half the time on crowded elements.  Interpolation: 28 to 280 us against
+// 15 to 24 at 1,000 points, level at kPointMax.  Mixed precision at the orders
+// that interpolate in binary32 stays on its own kernels at every size.
+inline bool small_call(const fp_handle *h, int npts)
+{
+    return npts <= kPointMax && !(h->precision == FP_PREC_MIXED && h->n1 <= kMixed32MaxN1);
+}
 
 // findpts / findpts_eval on a given workspace and stream (the public calls
 // pass the handle's own workspace; `timed` records the handle's events).

@@ -23,6 +23,7 @@
 #include "fp_basis.h"
 #include "fp_internal.h"
 #include "fp_mfma.h"
+#include "fp_wave.h"
 
 namespace fp {
 
@@ -59,8 +60,9 @@ struct LocArgs {
     int *res_in;
     unsigned *cand_part;  // per k_cand block: the method's candidates (first pass)
     unsigned *iter_part;  // per block: Newton iterations of its pairs
-    int pair_max;         // second pass, orders 1..7: up to this many pairs run on
-                          // k_newton_pair (one wavefront per pair), else 0
+    int pair_max;         // second pass: up to this many pairs run on k_newton_pair
+                          // (one wavefront per pair)
+    unsigned *pt_part;    // small calls: counters of each block
 };
 
 __device__ __forceinline__ int cell_of(const Grid &g, int a, double x)
@@ -505,6 +507,8 @@ __global__ __launch_bounds__(kWave) void k_locate(LocArgs a, const double *__res
                                                   const double *__restrict__ dnode)
 {
     if (a.only && !*a.gate) return;
+    // a short second pass runs on k_newton_pair
+    if (a.only && a.elem_off[a.E] <= a.pair_max) return;
     constexpr int V = N1 * N1 * N1;
     const BasisPtr<double> B{as_const(basis)};
     unsigned long long my_iters = 0;
@@ -570,6 +574,7 @@ __global__ __launch_bounds__(kWave) void k_locate(LocArgs a, const double *__res
 #include "fp_mixed8.inc"
 #include "fp_newton_pl.inc"
 #include "fp_pair.inc"
+#include "fp_point.inc"
 
 constexpr int kStatsBlocks = 32;
 
@@ -741,10 +746,20 @@ static hipError_t launch_locate_kernel(const fp_handle *h, const LocArgs &a, int
 {
 #define FP_GRID(K) (a.only ? std::min(unit_grid(h->E, n, (K)), kSecondPassGrid) \
                            : unit_grid(h->E, n, (K)))
+// a second pass of few pairs: one wavefront per pair
+#define FP_LAUNCH_PAIR(N1)                                                  \
+    do {                                                                    \
+        if constexpr (N1 <= kN8) {                                          \
+            if (a.only) k_newton_pair<N1><<<*nblk, kWave, 0, s>>>(a, h->d_basis);      \
+        } else {                                                            \
+            if (a.only) k_newton_pair_rows<N1><<<*nblk, kWave, 0, s>>>(a, h->d_basis); \
+        }                                                                   \
+    } while (0)
 #define FP_LAUNCH_LOCATE(N1)                                      \
     do {                                                          \
         *nblk = FP_GRID(kUnitScalar);                             \
         k_locate<N1><<<*nblk, kWave, 0, s>>>(a, h->d_basis, h->d_dnode); \
+        FP_LAUNCH_PAIR(N1);                                       \
     } while (0)
 // mixed precision: first pass only (the second pass is binary64).  At order 5
 // the binary64 kernel (two wavefronts per SIMD) is faster than the binary32
@@ -767,8 +782,7 @@ constexpr int kBinary64Only = 6;
             *nblk = FP_GRID(kUnitMfma);                                              \
             k_locate_mfma<N1><<<*nblk, kWave, 0, s>>>(a, h->d_basis, h->d_dnode);     \
         }                                                                            \
-        if (a.only && a.pair_max > 0)                                                \
-            k_newton_pair<N1><<<*nblk, kWave, 0, s>>>(a, h->d_basis);                 \
+        FP_LAUNCH_PAIR(N1);                                                          \
     } while (0)
 // orders 8 and 9: matrix cores, one plane per lane; mixed precision (first
 // pass): a binary32 phase, then binary64 Newton from its end points
@@ -782,6 +796,7 @@ constexpr int kBinary64Only = 6;
         } else                                                                        \
             k_newton_pl<N1, false><<<*nblk, 2 * kWave, 0, s>>>(a, h->d_basis, h->d_basis32, \
                                                               h->d_dnode);            \
+        FP_LAUNCH_PAIR(N1);                                                           \
     } while (0)
     switch (h->n1) {
         case 2: FP_LAUNCH_MFMA(2); break;
@@ -802,9 +817,24 @@ constexpr int kBinary64Only = 6;
         default: return hipErrorInvalidValue;
     }
 #undef FP_LAUNCH_LOCATE
+#undef FP_LAUNCH_PAIR
 #undef FP_LAUNCH_MFMA
 #undef FP_LAUNCH_PL
 #undef FP_GRID
+    return hipGetLastError();
+}
+
+// A small call's pass in one kernel (and the fold of its counters).
+static hipError_t launch_point(const fp_handle *h, const LocArgs &a, int *code, int *el,
+                               double *rst, double *dist2, hipStream_t s)
+{
+    const int nblk = a.npts < kPointMax ? a.npts : kPointMax;
+#define FP_POINT(N1) k_point<N1><<<nblk, kWave, 0, s>>>(a, h->d_basis, code, el, rst, dist2)
+    FP_DISPATCH_N1(h->n1, FP_POINT)
+#undef FP_POINT
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    k_point_stats<<<1, 1024, 0, s>>>(a.pt_part, nblk, a.npts, h->stats);
     return hipGetLastError();
 }
 
@@ -851,6 +881,7 @@ int run_findpts(fp_handle *h, const Work &w, int npts, const double *pts, const 
         a.cand_part = w.cand_part;
         a.iter_part = w.iter_part;
         a.gate = w.gate;
+        a.pt_part = w.pt_part;
 
         hipEvent_t t0 = nullptr, t1 = nullptr, l0 = nullptr, l1 = nullptr;
         if (timed) {
@@ -868,6 +899,17 @@ int run_findpts(fp_handle *h, const Work &w, int npts, const double *pts, const 
         // second pass
         a.obb = h->obb;
         a.redo = w.redo;
+        if (small_call(h, npts)) {
+            if (timed) FP_HIP(hipEventRecord(l0, s));
+            FP_HIP(launch_point(h, a, co, eo, ro, dO, s));
+            if (timed) {
+                FP_HIP(hipEventRecord(l1, s));
+                FP_HIP(hipEventRecord(t1, s));
+                record(h, 0, l0, l1);
+                record(h, 2, t0, t1);
+            }
+            continue;
+        }
         FP_HIP(fill_int(w.elem_cnt, 0, (long long)h->E + 1, s));
         k_cand<<<pb, 256, 0, s>>>(a);
         FP_HIP(hipGetLastError());
@@ -888,7 +930,7 @@ int run_findpts(fp_handle *h, const Work &w, int npts, const double *pts, const 
         a.obb = nullptr;
         a.redo = nullptr;
         a.only = w.redo;
-        a.pair_max = h->n1 <= kN8 ? kPairMax : 0;
+        a.pair_max = kPairMax;
         FP_HIP(fill_int_gated(w.elem_cnt, 0, (long long)h->E + 1, w.gate, s));
         k_cand<<<pb, 256, 0, s>>>(a);
         FP_HIP(hipGetLastError());

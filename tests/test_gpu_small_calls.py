@@ -1,0 +1,102 @@
+"""Small calls (one wavefront per point) and calls just past their limit (the
+element-grouped path), at every order: the same points through both paths
+against the CPU oracle, under the parity rules of the other GPU tests."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads as w
+from parity import compare_eval, compare_locate
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-12
+LIMIT = 16384  # kPointMax of the library
+
+
+def _points(n, seed):
+    """Around an annulus 0.5 <= rho <= 1: inside, off its walls, outside."""
+    rng = np.random.default_rng(seed)
+    rho = np.sqrt(rng.uniform(0.24, 1.02, n))
+    th = rng.uniform(0.0, 2.0 * np.pi, n)
+    p = np.stack([rho * np.cos(th), rho * np.sin(th), rng.uniform(-0.005, 1.005, n)], 1)
+    p[0] = np.nan
+    return p
+
+
+def _call(fp, h, pts, tags, fields):
+    code, el, rst, d2 = fp.findpts(h, pts, tags)
+    out = fp.findpts_eval(h, code, el, rst, fields)
+    torch.cuda.synchronize()
+    return [t.cpu().numpy() for t in (code, el, rst, d2)], out.cpu().numpy()
+
+
+@pytest.mark.parametrize("N", list(range(1, 16)))
+def test_both_paths_match_oracle(N):
+    from paper_1811_04891_amd import findpts as fp
+    print(f"case: small calls and a grouped call, order {N}", flush=True)
+    dev = torch.device("cuda:0")
+    mesh = w.annulus_mesh(2, 10, 2, N=N)
+    fields, _ = w.poly_fields(mesh, 5, degree=3, seed=N)
+    n = LIMIT + 1
+    pts = _points(n, N)
+    md = mesh.to(dev)
+    h = fp.findpts_setup(md.x, md.y, md.z, N, tol=TOL, max_points=n)
+    dp, df = torch.as_tensor(pts).to(dev), [f.to(dev) for f in fields]
+    fp.findpts_stats(h, reset=True)
+    big, big_out = _call(fp, h, dp, None, df)
+    cands = fp.findpts_stats(h, reset=True)[3]
+    # the oracle on every 16th point; codes and elements of all of them must
+    # be those of the small calls
+    om = oracle.OracleMesh.from_mesh(mesh, TOL)
+    _, hs = om.bbox()
+    sub = np.arange(0, n, 16)
+    ref = om.findpts(pts[sub])
+    hf = [f.numpy() for f in fields]
+    compare_locate(om, pts[sub], [a[sub] for a in big], ref, hs, TOL)
+    parts = [_call(fp, h, dp[a:b].contiguous(), None, df)
+             for a, b in ((0, 1), (1, 64), (64, n))]
+    st = fp.findpts_stats(h)
+    assert st[2] == n and st[3] == cands
+    small = [np.concatenate([p[0][k] for p in parts]) for k in range(4)]
+    small_out = np.concatenate([p[1] for p in parts], axis=1)
+    compare_locate(om, pts[sub], [a[sub] for a in small], ref, hs, TOL)
+    assert np.array_equal(big[0], small[0])
+    assert np.mean(big[1] != small[1]) <= 1e-3  # ties between border elements only
+    for res, out in ((big, big_out), (small, small_out)):
+        exp = om.eval(res[0][sub], res[1][sub], res[2][sub], hf)
+        compare_eval(out[:, sub], exp, hf)
+    h.free()
+
+
+@pytest.mark.parametrize("N", [2, 7, 9, 12])
+@pytest.mark.parametrize("nf", [1, 4, 5, 9])
+def test_small_call_sessions_and_field_counts(N, nf):
+    """Two overlapping annuli with the distance field, tagged and untagged
+    points, several field counts (one and two launches)."""
+    from paper_1811_04891_amd import findpts as fp
+    print(f"case: small call, sessions, order {N}, {nf} fields", flush=True)
+    dev = torch.device("cuda:0")
+    a = w.annulus_mesh(2, 10, 2, 0.5, 0.8, N=N)
+    b = w.annulus_mesh(2, 12, 3, 0.7, 1.0, N=N)
+    x, y, z = (torch.cat([getattr(a, c), getattr(b, c)]) for c in "xyz")
+    sess = torch.cat([torch.zeros(a.E, dtype=torch.int32), torch.ones(b.E, dtype=torch.int32)])
+    rho = torch.sqrt(x * x + y * y)
+    delta = torch.where(sess[:, None, None, None] == 0, 0.8 - rho, rho - 0.7).contiguous()
+    mesh = w.Mesh("two", N, x, y, z, sess, delta)
+    fields, _ = w.poly_fields(mesh, nf, degree=2, seed=3)
+    pts = _points(1501, 5)
+    tags = torch.as_tensor((np.arange(1501) % 3 - 1).astype(np.int32))
+    md = mesh.to(dev)
+    h = fp.findpts_setup(md.x, md.y, md.z, N, tol=TOL, elem_session=md.session, delta=md.delta,
+                         max_points=700)
+    res, out = _call(fp, h, torch.as_tensor(pts).to(dev), tags.to(dev), [f.to(dev) for f in fields])
+    om = oracle.OracleMesh.from_mesh(mesh, TOL)
+    _, hs = om.bbox()
+    ref = om.findpts(pts, tags.numpy())
+    st = compare_locate(om, pts, res, ref, hs, TOL)
+    assert st["inside"] > 500
+    hf = [f.numpy() for f in fields]
+    compare_eval(out, om.eval(res[0], res[1], res[2], hf), hf)
+    h.free()
