@@ -107,7 +107,7 @@ FP_API int findpts_setup(fp_handle **h, const double *x, const double *y,
  *   delta    new distance field (E*(N+1)^3) or NULL to keep the current one;
  *            FP_ESTATE if the handle was set up without one.
  * Allocates only when the new hash grid needs more room than any earlier
- * one.  Synchronises `stream` three times.  Calls on the handle that are
+ * one.  Synchronises `stream` two or three times.  Calls on the handle that are
  * still in flight must have finished (the serving layer must not be running
  * requests on it; requests queued on it count as in flight: if the update
  * lengthens the longest hash-cell list, such a request later fails with
@@ -169,8 +169,7 @@ FP_API int findpts_eval_noalloc(fp_handle *h, int npts, const int *code, const i
                                 const double *const *h_fields, double *out, void *stream);
 
 /* Switch precision (fp_precision) for later calls; FP_EINVAL if unknown.
- * Mixed precision needs no new allocation: the binary32 geometry copy is
- * built at setup. */
+ * Needs no new allocation. */
 FP_API int findpts_set_precision(fp_handle *h, int precision);
 
 /*

@@ -69,6 +69,14 @@ struct Grid {
     int nc[3];
 };
 
+// What a build's kernels tell the host.
+struct SetupRead {
+    double box[6];  // union of the element boxes
+    int bad;        // a node coordinate is not finite
+    int nnz;        // entries of the hash cells
+    int maxlen;     // longest cell list
+};
+
 struct TimedPair {
     int phase;
     hipEvent_t a, b;
@@ -119,14 +127,12 @@ struct fp_handle {
 
     // mesh (handle-owned)
     double *geom = nullptr;    // E x 3 x V, element-blocked, r index fastest
-    float *geom32 = nullptr;   // binary32 copy (mixed precision)
     double *esize = nullptr;   // E: h_e
     double *bbox = nullptr;    // E x 6
     double *erec = nullptr;    // E x 16 doubles (one 128-byte line per element): the
                                // axis-aligned box (6 doubles) then the oriented box
-                               // (18 binary32 values), for the candidate tests
-    float *obb = nullptr;      // E x 18 binary32: frame Q (9, row-major, rows = axes),
-                               // centre (3), rotated lo (3), rotated hi (3)
+                               // (18 binary32 values: frame Q, row-major, rows = axes,
+                               // centre, rotated lo, rotated hi), for the candidate tests
     int *esess = nullptr;      // E or null
     double *delta = nullptr;   // E x V or null
 
@@ -146,8 +152,9 @@ struct fp_handle {
     fp::Work work{};
     void *work_mem = nullptr;
     size_t work_bytes = 0;
-    int *d_flag = nullptr;      // setup scratch: flags, longest cell list
-    double *d_g = nullptr;      // setup scratch: global box
+    int2 *cell_raw = nullptr;   // nnz: (element, cell) per entry, unsorted (hash build)
+    int *d_flag = nullptr;      // hash build: non-finite flag (zero between builds)
+    fp::SetupRead *h_read = nullptr;  // pinned host memory the build's kernels write
     double *d_binv = nullptr;   // Bernstein-to-nodal inverse (n1 x n1)
     int *scan_tmp = nullptr;    // setup's scans (cells)
     int scan_tmp_n = 0;

@@ -30,7 +30,7 @@ namespace fp {
 struct LocArgs {
     const double *geom;
     const double *esize;
-    const float *obb;    // non-null: also test the oriented box (first pass)
+    bool first;          // first pass: also test the oriented box
     const double *erec;  // per element, 16 doubles: axis-aligned box, oriented box
     int *redo;           // first pass writes 1 for tasks left without an inside
                          // candidate and with a partial candidate set, else 0
@@ -102,7 +102,7 @@ constexpr int kCountMask = (1 << kFullBit) - 1;
 __global__ __launch_bounds__(256) void k_cand(LocArgs a)
 {
     if (a.only && !*a.gate) return;  // second pass with nothing flagged
-    if (a.obb && blockIdx.x == 0 && threadIdx.x == 0) *a.gate = 0;
+    if (a.first && blockIdx.x == 0 && threadIdx.x == 0) *a.gate = 0;
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     int naabb = 0, n = 0, n1st = 0;
     if (t < a.npts && a.only && !a.only[t]) {
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(256) void k_cand(LocArgs a)
         const double x0 = a.pts[3 * (long long)p], x1 = a.pts[3 * (long long)p + 1],
                      x2 = a.pts[3 * (long long)p + 2];
         const int ps = a.psess ? a.psess[p] : -1;
-        int full = a.obb ? 0 : 1;
+        int full = a.first ? 0 : 1;
         bool take = true;
         if (a.only) {  // second pass: the first pass's candidates stay in their slots
             n1st = a.ncand[t] & kCountMask;
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(256) void k_cand(LocArgs a)
             // pass 0: oriented-box filter (first pass only); pass 1: every
             // candidate, taken when the filter left none (the point then
             // has its full candidate set and needs no second pass)
-            for (int pass = a.obb ? 0 : 1; pass < 2 && (n == 0 || a.only); ++pass) {
+            for (int pass = a.first ? 0 : 1; pass < 2 && (n == 0 || a.only); ++pass) {
                 for (int q = qb; q < qe; ++q) {
                     // binary32 box (outward-rounded: a superset), then the
                     // exact binary64 box of the method
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(256) void k_cand(LocArgs a)
         const int r = wave_rank(a.elem_cnt, e, act);
         if (k < n) a.cand_pos[s] = act ? r : -1;
     }
-    if (a.obb) {  // the method's candidates of this block (first pass covers every point)
+    if (a.first) {  // the method's candidates of this block (first pass covers every point)
         __shared__ unsigned wsum[256 / kWave];
         unsigned v = (unsigned)naabb;
 #pragma unroll
@@ -700,7 +700,7 @@ __global__ __launch_bounds__(256) void k_select(LocArgs a, int *__restrict__ cod
         rst[3 * (long long)p + 2] = o[2];
         dist2[p] = o[3];
     }
-    if (a.obb) {
+    if (a.first) {
         bool redo = c != 0 && (!full || unsolved || outside);
         if (c == 0 && unsolved) {
             // a pair the binary32 phase left unsolved may be inside too: with
@@ -768,10 +768,10 @@ constexpr int kBinary64Only = 6;
 // mixed precision: first pass only (the second pass is binary64)
 #define FP_LAUNCH_MFMA(N1)                                                           \
     do {                                                                             \
-        if (h->precision == FP_PREC_MIXED && a.obb && N1 == kN8) {                   \
+        if (h->precision == FP_PREC_MIXED && a.first && N1 == kN8) {                   \
             *nblk = FP_GRID(kUnitMixed);                                             \
             k_mixed8<<<*nblk, kWave, 0, s>>>(a, h->d_basis, h->d_basis32, h->d_dnode); \
-        } else if (h->precision == FP_PREC_MIXED && a.obb && N1 != kBinary64Only) {  \
+        } else if (h->precision == FP_PREC_MIXED && a.first && N1 != kBinary64Only) {  \
             *nblk = FP_GRID(kUnitMixed);                                             \
             k_locate_mixed<N1><<<*nblk, kWave, 0, s>>>(a, h->d_basis, h->d_basis32,  \
                                                         h->d_dnode);                 \
@@ -789,7 +789,7 @@ constexpr int kBinary64Only = 6;
 #define FP_LAUNCH_PL(N1)                                                              \
     do {                                                                              \
         *nblk = FP_GRID(kUnitPl);                                                     \
-        if (h->precision == FP_PREC_MIXED && a.obb) {                                 \
+        if (h->precision == FP_PREC_MIXED && a.first) {                                 \
             k_mixed_pl<N1><<<*nblk, 2 * kWave, 0, s>>>(a, h->d_basis32, h->d_dnode); \
             k_newton_pl<N1, true><<<*nblk, 2 * kWave, 0, s>>>(a, h->d_basis, h->d_basis32, \
                                                              h->d_dnode);             \
@@ -897,7 +897,7 @@ int run_findpts(fp_handle *h, const Work &w, int npts, const double *pts, const 
         // first pass: oriented-box candidates; tasks without an inside
         // candidate (and with a partial candidate set) are flagged for the
         // second pass
-        a.obb = h->obb;
+        a.first = true;
         a.redo = w.redo;
         if (small_call(h, npts)) {
             if (timed) FP_HIP(hipEventRecord(l0, s));
@@ -927,7 +927,7 @@ int run_findpts(fp_handle *h, const Work &w, int npts, const double *pts, const 
         FP_HIP(hipGetLastError());
         // second pass over the flagged tasks with the axis-aligned candidates
         // only (other tasks get no candidates and keep their result)
-        a.obb = nullptr;
+        a.first = false;
         a.redo = nullptr;
         a.only = w.redo;
         a.pair_max = kPairMax;

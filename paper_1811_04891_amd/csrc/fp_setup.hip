@@ -7,7 +7,9 @@
 #include <string>
 #include <vector>
 
+#include "fp_basis.h"
 #include "fp_internal.h"
+#include "fp_wave.h"
 
 namespace fp {
 
@@ -131,267 +133,265 @@ std::vector<double> bernstein_to_nodal_inverse(int N, const double *z)
 // Kernels.
 // ---------------------------------------------------------------------------
 
-// Copy x, y, z (each E*V) into the element-blocked E x 3 x V layout (and the
-// binary32 copy), flagging non-finite values.
-__global__ __launch_bounds__(256) void k_pack(const double *__restrict__ x,
-                                              const double *__restrict__ y,
-                                              const double *__restrict__ z, long long EV,
-                                              int V, double *__restrict__ geom,
-                                              float *__restrict__ geom32,
-                                              int *__restrict__ bad)
+// Sums (the first nsum values) and minima over a block of W wavefronts, in
+// every thread.
+template <int W, int NV>
+__device__ __forceinline__ void block_reduce(double (&v)[NV], int nsum, double *lds)
 {
-    long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    long long stride = (long long)gridDim.x * blockDim.x;
+    static_assert(NV % 4 == 0, "four values at a time");
+#pragma unroll
+    for (int q = 0; q < NV; q += 4) {
+        if (q < nsum)
+            wave_sum4(v[q], v[q + 1], v[q + 2], v[q + 3]);
+        else
+            wave_min4(v[q], v[q + 1], v[q + 2], v[q + 3]);
+    }
+    if constexpr (W > 1) {
+        const int w = threadIdx.x / kWave;
+        __syncthreads();
+        if ((threadIdx.x & (kWave - 1)) == 0)
+#pragma unroll
+            for (int q = 0; q < NV; ++q) lds[w * NV + q] = v[q];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+            double r = lds[q];
+#pragma unroll
+            for (int o = 1; o < W; ++o)
+                r = (q < nsum) ? r + lds[o * NV + q] : fmin(r, lds[o * NV + q]);
+            v[q] = r;
+        }
+    }
+}
+
+// Everything setup keeps per element, in one pass over its nodes (one block
+// per element, one thread per node line): the packed copy, the axis-aligned
+// box, h_e, and the oriented box, with non-finite coordinates flagged.
+//
+// Axis-aligned box: min and max of the Bernstein coefficients of each
+// coordinate (the inverse nodal-Bernstein matrix applied along r, s, t), with
+// the margin 1e-8 h_e + 1e-14 max|x|.
+// Oriented box: the frame Q is the Gram-Schmidt basis of the mean edge vectors
+// along r, s, t (identity if they are degenerate).  The rotated coordinates
+// u = Q (x - centre) are linear in x and the transform keeps constants, so
+// their Bernstein coefficients are Q (b - centre) of the coordinates' own; any
+// Q (orthonormal or not) keeps the bound rigorous.  Margin: the axis-aligned
+// box's, or tol h_e if larger.  The record is binary32 (Q and the centre are
+// rounded first, the bounds are computed for the rounded frame, then rounded
+// outward) and shares a 128-byte line with the axis-aligned box.
+//
+// A line's n1 values stay in registers through its transform (n1^2
+// multiply-adds with the matrix in scalar registers); LDS only turns the lines
+// from one direction to the next (odd pitch: no bank conflicts).  The packing,
+// the two box kernels (each transforming three coordinates through LDS, two
+// LDS reads per multiply-add) and the record kernel that it replaces took 590
+// us on 16,384 elements of order 7, and setup kept a binary32 copy of the
+// coordinates that nothing read.
+template <int N1>
+struct ElemShape {
+    static constexpr int L = N1 * N1, V = L * N1;
+    static constexpr int W = (L + kWave - 1) / kWave;  // wavefronts per block
+    static constexpr int P = N1 | 1;                   // row pitch in LDS
+};
+
+template <int N1>
+__device__ __forceinline__ void bernstein_line(cptr<double> Bi, const double (&v)[N1],
+                                               double (&o)[N1])
+{
+#pragma unroll
+    for (int i = 0; i < N1; ++i) {
+        double s = 0.0;
+#pragma unroll
+        for (int l = 0; l < N1; ++l) s = fma(Bi[i * N1 + l], v[l], s);
+        o[i] = s;
+    }
+}
+
+template <int N1>
+__global__ __launch_bounds__(ElemShape<N1>::W *kWave) void k_elem(
+    const double *__restrict__ x, const double *__restrict__ y, const double *__restrict__ z,
+    const double *__restrict__ binv, double tol, double *__restrict__ geom,
+    double *__restrict__ bbox, double *__restrict__ esize, double *__restrict__ erec,
+    int *__restrict__ bad)
+{
+    using S = ElemShape<N1>;
+    constexpr int L = S::L, V = S::V, P = S::P, W = S::W;
+    __shared__ double sA[3 * L * P];
+    __shared__ double red[W * 28];
+    const long long e = blockIdx.x;
+    const int t = threadIdx.x;
+    const bool act = t < L;
+    const int row = act ? t : 0;
+    const int c0 = row % N1, c1 = row / N1;  // the line's two fixed indices, faster first
+    cptr<double> Bi = as_const(binv);
+    // 9 edge sums; node minima and maxima, coefficient minima and maxima, max|x|
+    double v[28];
+#pragma unroll
+    for (int q = 0; q < 28; ++q) v[q] = q < 12 ? 0.0 : INFINITY;
     int flag = 0;
-    for (; t < EV; t += stride) {
-        long long e = t / V, q = t - e * V;
-        double v0 = x[t], v1 = y[t], v2 = z[t];
-        flag |= !(isfinite(v0) && isfinite(v1) && isfinite(v2));
-        double *g = geom + e * 3 * V + q;
-        g[0] = v0;
-        g[V] = v1;
-        g[2 * V] = v2;
-        if (geom32) {
-            float *g32 = geom32 + e * 3 * V + q;
-            g32[0] = (float)v0;
-            g32[V] = (float)v1;
-            g32[2 * V] = (float)v2;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {  // lines along r: (j, k) = (c0, c1)
+        const double *src = (c == 0 ? x : (c == 1 ? y : z)) + e * V + row * N1;
+        double *dst = geom + (e * 3 + c) * V + row * N1;
+        double a[N1], o[N1];
+#pragma unroll
+        for (int i = 0; i < N1; ++i) a[i] = src[i];
+        double rs = 0.0;
+        if (act) {
+#pragma unroll
+            for (int i = 0; i < N1; ++i) {
+                dst[i] = a[i];
+                flag |= !isfinite(a[i]);
+                rs += a[i];
+                v[12 + c] = fmin(v[12 + c], a[i]);
+                v[15 + c] = fmin(v[15 + c], -a[i]);
+                v[24] = fmin(v[24], -fabs(a[i]));
+            }
+            v[c] = a[N1 - 1] - a[0];
+            v[3 + c] = (c0 == N1 - 1 ? rs : 0.0) - (c0 == 0 ? rs : 0.0);
+            v[6 + c] = (c1 == N1 - 1 ? rs : 0.0) - (c1 == 0 ? rs : 0.0);
+        }
+        bernstein_line<N1>(Bi, a, o);
+        if (act) {
+#pragma unroll
+            for (int i = 0; i < N1; ++i) sA[c * L * P + row * P + i] = o[i];
         }
     }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {  // lines along s: (i, k) = (c0, c1), in place
+        double a[N1], o[N1];
+        double *A = sA + c * L * P + N1 * c1 * P + c0;
+#pragma unroll
+        for (int j = 0; j < N1; ++j) a[j] = A[j * P];
+        bernstein_line<N1>(Bi, a, o);
+        if (act) {
+#pragma unroll
+            for (int j = 0; j < N1; ++j) A[j * P] = o[j];
+        }
+    }
+    __syncthreads();
+    double b[3][N1];  // Bernstein coefficients of the thread's line along t: (i, j) = (c0, c1)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        double a[N1];
+        const double *A = sA + c * L * P + c1 * P + c0;
+#pragma unroll
+        for (int k = 0; k < N1; ++k) a[k] = A[k * N1 * P];
+        bernstein_line<N1>(Bi, a, b[c]);
+#pragma unroll
+        for (int k = 0; k < N1; ++k) {  // (idle threads repeat line 0)
+            v[18 + c] = fmin(v[18 + c], b[c][k]);
+            v[21 + c] = fmin(v[21 + c], -b[c][k]);
+        }
+    }
+    block_reduce<W>(v, 12, red);
     if (flag) atomicOr(bad, 1);
-}
-
-__device__ __forceinline__ double wave_min(double v)
-{
+    double he = 0.0;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, kWave));
-    return v;
-}
-__device__ __forceinline__ double wave_max(double v)
-{
+    for (int c = 0; c < 3; ++c) he = fmax(he, -v[15 + c] - v[12 + c]);
+    const double m = 1e-8 * he + 1e-14 * -v[24];
+    double bb[6], ctr[3];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
-    return v;
-}
-
-// One wave per element: Bernstein coefficients of each coordinate (the
-// inverse nodal-Bernstein matrix applied along r, s, t in LDS), their min and
-// max, the node extents (h_e) and the margin 1e-8 h_e + 1e-14 max|x|.
-__global__ __launch_bounds__(kWave) void k_bbox(const double *__restrict__ geom, int n1,
-                                                const double *__restrict__ binv,
-                                                double *__restrict__ bbox,
-                                                double *__restrict__ esize)
-{
-    extern __shared__ double sh[];
-    const int V = n1 * n1 * n1;
-    double *A = sh, *B = sh + V;
-    __shared__ double Bi[kMaxN1 * kMaxN1];
-    const int e = blockIdx.x, t = threadIdx.x;
-    for (int q = t; q < n1 * n1; q += kWave) Bi[q] = binv[q];
-    double lo[3], hi[3], he = 0.0, amax = 0.0;
     for (int c = 0; c < 3; ++c) {
-        const double *X = geom + ((long long)e * 3 + c) * V;
-        double mn = INFINITY, mx = -INFINITY;
-        for (int q = t; q < V; q += kWave) {
-            double v = X[q];
-            A[q] = v;
-            mn = fmin(mn, v);
-            mx = fmax(mx, v);
-            amax = fmax(amax, fabs(v));
-        }
-        mn = wave_min(mn);
-        mx = wave_max(mx);
-        he = fmax(he, mx - mn);
-        __syncthreads();
-        for (int q = t; q < V; q += kWave) {  // along r
-            int i = q % n1, rest = q - i;
-            double s = 0.0;
-            for (int l = 0; l < n1; ++l) s = fma(Bi[i * n1 + l], A[rest + l], s);
-            B[q] = s;
-        }
-        __syncthreads();
-        for (int q = t; q < V; q += kWave) {  // along s
-            int i = q % n1, j = (q / n1) % n1, k = q / (n1 * n1);
-            double s = 0.0;
-            for (int l = 0; l < n1; ++l) s = fma(Bi[j * n1 + l], B[i + n1 * (l + n1 * k)], s);
-            A[q] = s;
-        }
-        __syncthreads();
-        double cmn = INFINITY, cmx = -INFINITY;
-        for (int q = t; q < V; q += kWave) {  // along t
-            int ij = q % (n1 * n1), k = q / (n1 * n1);
-            double s = 0.0;
-            for (int l = 0; l < n1; ++l) s = fma(Bi[k * n1 + l], A[ij + n1 * n1 * l], s);
-            cmn = fmin(cmn, s);
-            cmx = fmax(cmx, s);
-        }
-        lo[c] = wave_min(cmn);
-        hi[c] = wave_max(cmx);
-        __syncthreads();
-    }
-    amax = wave_max(amax);
-    if (t == 0) {
-        const double m = 1e-8 * he + 1e-14 * amax;
-        for (int c = 0; c < 3; ++c) {
-            bbox[6 * e + 2 * c] = lo[c] - m;
-            bbox[6 * e + 2 * c + 1] = hi[c] + m;
-        }
-        esize[e] = he;
-    }
-}
-
-// Oriented box of each element (one wave per element).  Frame: Gram-Schmidt
-// of the mean edge vectors along r, s, t (identity if they are degenerate).
-// The rotated coordinates u = Q (x - centre) are linear in x, so the
-// Bernstein coefficients of their nodal values bound the element in that
-// frame exactly as the axis-aligned box does; any Q (orthonormal or not)
-// keeps this rigorous.  Margin: the axis-aligned box's, or tol h_e if larger.  The record
-// is binary32 (72 bytes, half the binary64 one, for the candidate lookup's
-// memory traffic): Q and the centre are rounded first and the bounds are
-// computed for the rounded frame, then rounded outward.
-__global__ __launch_bounds__(kWave) void k_obb(const double *__restrict__ geom, int n1,
-                                               const double *__restrict__ binv,
-                                               const double *__restrict__ bbox,
-                                               const double *__restrict__ esize,
-                                               double tol, float *__restrict__ obb)
-{
-    extern __shared__ double sh[];
-    const int V = n1 * n1 * n1;
-    double *A = sh, *B = sh + V;
-    __shared__ double Bi[kMaxN1 * kMaxN1];
-    const int e = blockIdx.x, t = threadIdx.x;
-    for (int q = t; q < n1 * n1; q += kWave) Bi[q] = binv[q];
-    const double *X = geom + (long long)e * 3 * V;
-    // mean edge vectors (lane-parallel sums over the n1^2 node lines)
-    double ed[3][3];
-    for (int c = 0; c < 3; ++c) {
-        double sr = 0.0, ss = 0.0, st = 0.0;
-        for (int q = t; q < n1 * n1; q += kWave) {
-            const int a = q % n1, b = q / n1;
-            const double *Xc = X + c * V;
-            sr += Xc[n1 - 1 + n1 * (a + n1 * b)] - Xc[n1 * (a + n1 * b)];
-            ss += Xc[a + n1 * (n1 - 1 + n1 * b)] - Xc[a + n1 * n1 * b];
-            st += Xc[a + n1 * (b + n1 * (n1 - 1))] - Xc[a + n1 * b];
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            sr += __shfl_xor(sr, o, kWave);
-            ss += __shfl_xor(ss, o, kWave);
-            st += __shfl_xor(st, o, kWave);
-        }
-        ed[0][c] = sr;
-        ed[1][c] = ss;
-        ed[2][c] = st;
+        bb[2 * c] = v[18 + c] - m;
+        bb[2 * c + 1] = -v[21 + c] + m;
+        ctr[c] = (double)(float)(0.5 * (bb[2 * c] + bb[2 * c + 1]));
     }
     double Q[3][3];
     bool ok = true;
+#pragma unroll
     for (int a = 0; a < 3; ++a) {
-        double v[3] = {ed[a][0], ed[a][1], ed[a][2]};
-        for (int b = 0; b < a; ++b) {
-            const double d = v[0] * Q[b][0] + v[1] * Q[b][1] + v[2] * Q[b][2];
-            for (int c = 0; c < 3; ++c) v[c] -= d * Q[b][c];
+        double w[3] = {v[3 * a], v[3 * a + 1], v[3 * a + 2]};
+        const double ne = sqrt(w[0] * w[0] + w[1] * w[1] + w[2] * w[2]);
+#pragma unroll
+        for (int q = 0; q < a; ++q) {
+            const double d = w[0] * Q[q][0] + w[1] * Q[q][1] + w[2] * Q[q][2];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) w[c] -= d * Q[q][c];
         }
-        const double nv = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-        const double ne = sqrt(ed[a][0] * ed[a][0] + ed[a][1] * ed[a][1] + ed[a][2] * ed[a][2]);
+        const double nv = sqrt(w[0] * w[0] + w[1] * w[1] + w[2] * w[2]);
         ok = ok && isfinite(nv) && nv > 1e-6 * ne && ne > 0.0;
-        for (int c = 0; c < 3; ++c) Q[a][c] = ok ? v[c] / nv : 0.0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) Q[a][c] = ok ? w[c] / nv : 0.0;
     }
-    if (!ok)
-        for (int a = 0; a < 3; ++a)
-            for (int c = 0; c < 3; ++c) Q[a][c] = (a == c) ? 1.0 : 0.0;
+#pragma unroll
     for (int a = 0; a < 3; ++a)
-        for (int c = 0; c < 3; ++c) Q[a][c] = (double)(float)Q[a][c];
-    const double *bb = bbox + 6 * (long long)e;
-    const double ctr[3] = {(double)(float)(0.5 * (bb[0] + bb[1])),
-                           (double)(float)(0.5 * (bb[2] + bb[3])),
-                           (double)(float)(0.5 * (bb[4] + bb[5]))};
-    double lo[3], hi[3], amax = 0.0;
-    for (int a = 0; a < 3; ++a) {
-        for (int q = t; q < V; q += kWave) {
-            const double u = Q[a][0] * (X[q] - ctr[0]) + Q[a][1] * (X[V + q] - ctr[1]) +
-                             Q[a][2] * (X[2 * V + q] - ctr[2]);
-            A[q] = u;
-            amax = fmax(amax, fabs(u));
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            Q[a][c] = ok ? (double)(float)Q[a][c] : (a == c ? 1.0 : 0.0);
+    double u[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) u[q] = INFINITY;
+#pragma unroll
+    for (int k = 0; k < N1; ++k) {
+        const double d0 = b[0][k] - ctr[0], d1 = b[1][k] - ctr[1], d2 = b[2][k] - ctr[2];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const double w = Q[a][0] * d0 + Q[a][1] * d1 + Q[a][2] * d2;
+            u[a] = fmin(u[a], w);
+            u[3 + a] = fmin(u[3 + a], -w);
+            u[6] = fmin(u[6], -fabs(w));
         }
-        __syncthreads();
-        for (int q = t; q < V; q += kWave) {  // along r
-            int i = q % n1, rest = q - i;
-            double s = 0.0;
-            for (int l = 0; l < n1; ++l) s = fma(Bi[i * n1 + l], A[rest + l], s);
-            B[q] = s;
-        }
-        __syncthreads();
-        for (int q = t; q < V; q += kWave) {  // along s
-            int i = q % n1, j = (q / n1) % n1, k = q / (n1 * n1);
-            double s = 0.0;
-            for (int l = 0; l < n1; ++l) s = fma(Bi[j * n1 + l], B[i + n1 * (l + n1 * k)], s);
-            A[q] = s;
-        }
-        __syncthreads();
-        double cmn = INFINITY, cmx = -INFINITY;
-        for (int q = t; q < V; q += kWave) {  // along t
-            int ij = q % (n1 * n1), k = q / (n1 * n1);
-            double s = 0.0;
-            for (int l = 0; l < n1; ++l) s = fma(Bi[k * n1 + l], A[ij + n1 * n1 * l], s);
-            cmn = fmin(cmn, s);
-            cmx = fmax(cmx, s);
-        }
-        lo[a] = wave_min(cmn);
-        hi[a] = wave_max(cmx);
-        __syncthreads();
     }
-    amax = wave_max(amax);
+    block_reduce<W>(u, 0, red);
     if (t == 0) {
         const double cabs = fmax(fabs(ctr[0]), fmax(fabs(ctr[1]), fabs(ctr[2])));
         // the axis-aligned box's margin, or the inside tolerance when that is
         // larger (a point within tol h_e of the element may be inside; the
         // rounded frame's rows have norm 1 to within 1e-7)
-        const double m = fmax(1e-8, (1.0 + 1e-6) * tol) * esize[e] + 1e-14 * (amax + cabs);
-        float *o = obb + 18 * (long long)e;
-        for (int a = 0; a < 3; ++a)
+        const double mo = fmax(1e-8, (1.0 + 1e-6) * tol) * he + 1e-14 * (-u[6] + cabs);
+        double *r = erec + 16 * e;
+        float *o = (float *)(r + 6);
+        esize[e] = he;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            bbox[6 * e + q] = bb[q];
+            r[q] = bb[q];
+        }
+        r[15] = 0.0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+#pragma unroll
             for (int c = 0; c < 3; ++c) o[3 * a + c] = (float)Q[a][c];  // exact
-        for (int c = 0; c < 3; ++c) {
-            o[9 + c] = (float)ctr[c];  // exact
-            const double l = lo[c] - m, u = hi[c] + m;
-            float lf = (float)l, uf = (float)u;
+            o[9 + a] = (float)ctr[a];                                   // exact
+            const double l = u[a] - mo, h = -u[3 + a] + mo;
+            float lf = (float)l, hf = (float)h;
             if ((double)lf > l) lf = nextafterf(lf, -INFINITY);
-            if ((double)uf < u) uf = nextafterf(uf, INFINITY);
-            o[12 + c] = lf;
-            o[15 + c] = uf;
+            if ((double)hf < h) hf = nextafterf(hf, INFINITY);
+            o[12 + a] = lf;
+            o[15 + a] = hf;
         }
     }
 }
 
-// Union of the element boxes (one block).
-__global__ __launch_bounds__(256) void k_gbox(const double *__restrict__ bbox, int E,
-                                              double *__restrict__ out)
+// Union of the element boxes (one block) and the non-finite flag, written to
+// the handle's pinned host record; the flag is cleared for the next build.
+__global__ __launch_bounds__(1024) void k_gbox(const double *__restrict__ bbox, int E,
+                                               int *__restrict__ bad, SetupRead *__restrict__ rd)
 {
-    __shared__ double red[6][256 / kWave];
-    double v[6] = {INFINITY, -INFINITY, INFINITY, -INFINITY, INFINITY, -INFINITY};
-    for (int e = threadIdx.x; e < E; e += blockDim.x)
+    __shared__ double red[(1024 / kWave) * 8];
+    double v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = INFINITY;
+#pragma unroll 4
+    for (int e = threadIdx.x; e < E; e += 1024) {
+        const double *b = bbox + 6 * (long long)e;
+#pragma unroll
         for (int a = 0; a < 3; ++a) {
-            v[2 * a] = fmin(v[2 * a], bbox[6 * e + 2 * a]);
-            v[2 * a + 1] = fmax(v[2 * a + 1], bbox[6 * e + 2 * a + 1]);
-        }
-    const int w = threadIdx.x / kWave;
-    for (int a = 0; a < 3; ++a) {
-        double mn = wave_min(v[2 * a]), mx = wave_max(v[2 * a + 1]);
-        if ((threadIdx.x & (kWave - 1)) == 0) {
-            red[2 * a][w] = mn;
-            red[2 * a + 1][w] = mx;
+            v[2 * a] = fmin(v[2 * a], b[2 * a]);
+            v[2 * a + 1] = fmin(v[2 * a + 1], -b[2 * a + 1]);
         }
     }
-    __syncthreads();
+    block_reduce<1024 / kWave>(v, 0, red);
     if (threadIdx.x == 0) {
+#pragma unroll
         for (int a = 0; a < 3; ++a) {
-            double mn = red[2 * a][0], mx = red[2 * a + 1][0];
-            for (int q = 1; q < (int)(blockDim.x / kWave); ++q) {
-                mn = fmin(mn, red[2 * a][q]);
-                mx = fmax(mx, red[2 * a + 1][q]);
-            }
-            out[2 * a] = mn;
-            out[2 * a + 1] = mx;
+            rd->box[2 * a] = v[2 * a];
+            rd->box[2 * a + 1] = -v[2 * a + 1];
         }
+        rd->bad = *bad;
+        *bad = 0;
     }
 }
 
@@ -402,86 +402,98 @@ __device__ __forceinline__ int cell_axis(const Grid &g, int a, double x)
     return i < 0 ? 0 : (i >= g.nc[a] ? g.nc[a] - 1 : i);
 }
 
-// mode 0: count entries per cell; mode 1: write element ids.
+// One wavefront per element, its lanes over the cells its box meets.  Pass 0
+// counts the entries per cell; pass 1 takes each entry's place from the counts
+// (counting down) and writes (element, cell) there, unless the lists outgrew
+// the room for them (the host then makes room and repeats the pass).
 __global__ __launch_bounds__(256) void k_hash_pass(const double *__restrict__ bbox, int E,
-                                                   Grid g, int mode, int *__restrict__ cnt,
+                                                   Grid g, int pass, int *__restrict__ cnt,
                                                    const int *__restrict__ off,
-                                                   int *__restrict__ cell_el)
+                                                   int2 *__restrict__ raw, long long cap)
 {
-    int e = blockIdx.x * blockDim.x + threadIdx.x;
+    const int e = blockIdx.x * (256 / kWave) + threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
     if (e >= E) return;
-    const double *b = bbox + 6 * e;
-    int i0 = cell_axis(g, 0, b[0]), i1 = cell_axis(g, 0, b[1]);
-    int j0 = cell_axis(g, 1, b[2]), j1 = cell_axis(g, 1, b[3]);
-    int k0 = cell_axis(g, 2, b[4]), k1 = cell_axis(g, 2, b[5]);
-    for (int k = k0; k <= k1; ++k)
-        for (int j = j0; j <= j1; ++j)
-            for (int i = i0; i <= i1; ++i) {
-                long long c = i + (long long)g.nc[0] * (j + (long long)g.nc[1] * k);
-                int pos = atomicAdd(&cnt[c], 1);
-                if (mode == 1) cell_el[off[c] + pos] = e;
-            }
-}
-
-// Sort each cell list ascending (insertion sort; lists are short) and find
-// the longest list.
-__global__ __launch_bounds__(256) void k_hash_sort(const int *__restrict__ off,
-                                                   int *__restrict__ cell_el, long long ncell,
-                                                   int *__restrict__ maxlen)
-{
-    long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= ncell) return;
-    int b = off[c], n = off[c + 1] - b;
-    int *L = cell_el + b;
-    for (int i = 1; i < n; ++i) {
-        int v = L[i], j = i - 1;
-        while (j >= 0 && L[j] > v) {
-            L[j + 1] = L[j];
-            --j;
-        }
-        L[j + 1] = v;
-    }
-    atomicMax(maxlen, n);
-}
-
-// One 128-byte record per element for the candidate lookup: the binary64
-// axis-aligned box and the binary32 oriented box share a cache line.
-__global__ __launch_bounds__(256) void k_erec(const double *__restrict__ bbox,
-                                              const float *__restrict__ obb, int E,
-                                              double *__restrict__ erec)
-{
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= E) return;
-    double *r = erec + 16 * (long long)e;
-    for (int i = 0; i < 6; ++i) r[i] = bbox[6 * (long long)e + i];
-    float *o = (float *)(r + 6);
-    for (int i = 0; i < 18; ++i) o[i] = obb[18 * (long long)e + i];
-    r[15] = 0.0;
-}
-
-// Per cell-list entry, the element's box in binary32 rounded outward (never
-// smaller than the binary64 box) with the element id in the spare slot: the
-// candidate lookup streams a cell's entries contiguously and tests the exact
-// binary64 box only for the survivors.
-__global__ __launch_bounds__(256) void k_cellbox(const double *__restrict__ bbox,
-                                                 const int *__restrict__ cell_el, long long nnz,
-                                                 float4 *__restrict__ cell_box)
-{
-    const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= nnz) return;
-    const int e = cell_el[q];
     const double *b = bbox + 6 * (long long)e;
-    float lo[3], hi[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        float l = (float)b[2 * a], u = (float)b[2 * a + 1];
-        if ((double)l > b[2 * a]) l = nextafterf(l, -INFINITY);
-        if ((double)u < b[2 * a + 1]) u = nextafterf(u, INFINITY);
-        lo[a] = l;
-        hi[a] = u;
+    const int i0 = cell_axis(g, 0, b[0]), i1 = cell_axis(g, 0, b[1]);
+    const int j0 = cell_axis(g, 1, b[2]), j1 = cell_axis(g, 1, b[3]);
+    const int k0 = cell_axis(g, 2, b[4]), k1 = cell_axis(g, 2, b[5]);
+    const int ni = i1 - i0 + 1, nj = j1 - j0 + 1;
+    const int n = ni * nj * (k1 - k0 + 1);  // at most 1024^3 cells in all
+    if (pass == 1 && off[(long long)g.nc[0] * g.nc[1] * g.nc[2]] > cap) return;
+    for (int q = lane; q < n; q += kWave) {
+        const int i = i0 + q % ni, j = j0 + q / ni % nj, k = k0 + q / (ni * nj);
+        const long long c = i + (long long)g.nc[0] * (j + (long long)g.nc[1] * k);
+        if (pass == 0)
+            atomicAdd(&cnt[c], 1);
+        else
+            raw[off[c] + atomicSub(&cnt[c], 1) - 1] = make_int2(e, (int)c);
     }
-    cell_box[2 * q] = make_float4(lo[0], lo[1], lo[2], __int_as_float(e));
-    cell_box[2 * q + 1] = make_float4(hi[0], hi[1], hi[2], 0.0f);
+}
+
+// Each entry to its place in its cell's ascending list (its rank among the
+// list's elements: lists are short), with the element's box in binary32
+// rounded outward (never smaller than the binary64 box) and the element id in
+// the spare slot: the candidate lookup streams a cell's entries contiguously
+// and tests the exact binary64 box only for the survivors.  Also the longest
+// list of each block, into the counters (pass 1 has counted them down; an
+// atomic maximum over the wavefronts took 45 us on one address).
+__global__ __launch_bounds__(256) void k_hash_place(const double *__restrict__ bbox,
+                                                    const int *__restrict__ off, long long ncell,
+                                                    const int2 *__restrict__ raw, long long cap,
+                                                    int *__restrict__ cell_el,
+                                                    float4 *__restrict__ cell_box,
+                                                    int *__restrict__ longest_of)
+{
+    const long long nnz = off[ncell];
+    if (nnz > cap) return;
+    int longest = 0;
+    for (long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x; q < nnz;
+         q += (long long)gridDim.x * blockDim.x) {
+        const int2 me = raw[q];
+        const int b = off[me.y], n = off[me.y + 1] - b;
+        int rank = 0;
+        for (int j = 0; j < n; ++j) rank += raw[b + j].x < me.x ? 1 : 0;
+        longest = max(longest, n);
+        const double *x = bbox + 6 * (long long)me.x;
+        float lo[3], hi[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            float l = (float)x[2 * a], u = (float)x[2 * a + 1];
+            if ((double)l > x[2 * a]) l = nextafterf(l, -INFINITY);
+            if ((double)u < x[2 * a + 1]) u = nextafterf(u, INFINITY);
+            lo[a] = l;
+            hi[a] = u;
+        }
+        const long long to = b + rank;
+        cell_el[to] = me.x;
+        cell_box[2 * to] = make_float4(lo[0], lo[1], lo[2], __int_as_float(me.x));
+        cell_box[2 * to + 1] = make_float4(hi[0], hi[1], hi[2], 0.0f);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) longest = max(longest, __shfl_xor(longest, o, kWave));
+    __shared__ int red[256 / kWave];
+    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = longest;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 256 / kWave; ++w) longest = max(longest, red[w]);
+        longest_of[blockIdx.x] = longest;
+    }
+}
+
+// Entry count and longest list to the pinned host record (one wavefront).
+__global__ __launch_bounds__(kWave) void k_hash_read(const int *__restrict__ off, long long ncell,
+                                                     const int *__restrict__ longest_of, int nblk,
+                                                     SetupRead *__restrict__ rd)
+{
+    int m = 0;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < nblk; i += kWave) m = max(m, longest_of[i]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, kWave));
+    if (threadIdx.x == 0) {
+        rd->nnz = off[ncell];
+        rd->maxlen = m;
+    }
 }
 
 }  // namespace fp
@@ -558,12 +570,13 @@ using namespace fp;
 
 static void release(fp_handle *h)
 {
-    void *ptrs[] = {h->d_basis, h->d_basis32, h->geom, h->geom32, h->esize, h->bbox, h->obb,
-                    h->esess, h->delta, h->cell_off, h->cell_cnt, h->cell_el, h->cell_box,
-                    h->work_mem, h->scan_tmp, h->stats, h->d_flag, h->d_g, h->d_binv,
-                    h->d_dnode, h->erec};
+    void *ptrs[] = {h->d_basis, h->d_basis32, h->geom, h->esize, h->bbox, h->esess, h->delta,
+                    h->cell_off, h->cell_cnt, h->cell_el, h->cell_box, h->cell_raw,
+                    h->work_mem, h->scan_tmp, h->stats, h->d_flag, h->d_binv, h->d_dnode,
+                    h->erec};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
+    if (h->h_read) (void)hipHostFree(h->h_read);
     for (auto &t : h->timed) {
         (void)hipEventDestroy(t.a);
         (void)hipEventDestroy(t.b);
@@ -591,39 +604,50 @@ static hipError_t dalloc(fp_handle *h, T **p, size_t count)
         }                                           \
     } while (0)
 
-// Geometry products of the current node coordinates: packed copies, element
+// Geometry products of the current node coordinates: packed copy, element
 // boxes and sizes, oriented boxes, hash grid (with the per-entry binary32
 // boxes) and the longest cell list.  Device arrays keep their allocation when
 // large enough (an update of a moving mesh allocates only when its hash needs
-// more room than before).  Synchronises `s` three times (global box, entry
-// count, longest list).
+// more room than before).  Synchronises `s` for the global box (the grid is
+// laid out on the host) and for the entry count and longest list, once more
+// when the entries need more room than there is.  What the host reads is
+// written by the kernels to pinned host memory (three copies to pageable
+// memory cost 250 us of an update's 0.9 ms in gaps).
 static int build_geometry(fp_handle *h, const double *x, const double *y, const double *z,
                           hipStream_t s, const char *who)
 {
     const int E = h->E;
-    const long long V = h->V, EV = (long long)E * V;
-    const int n1 = h->n1;
-    FP_HIP(hipMemsetAsync(h->d_flag, 0, sizeof(int), s));
-    {
-        long long blocks = std::min<long long>((EV + 255) / 256, 256LL * 64);
-        k_pack<<<(int)blocks, 256, 0, s>>>(x, y, z, EV, (int)V, h->geom, h->geom32, h->d_flag);
-        FP_HIP(hipGetLastError());
+    int *bad = h->d_flag;
+#define FP_ELEM(N1)                                                                         \
+    case N1:                                                                                \
+        k_elem<N1><<<E, ElemShape<N1>::W * kWave, 0, s>>>(x, y, z, h->d_binv, h->tol, h->geom, \
+                                                          h->bbox, h->esize, h->erec, bad); \
+        break
+    switch (h->n1) {
+        FP_ELEM(2);
+        FP_ELEM(3);
+        FP_ELEM(4);
+        FP_ELEM(5);
+        FP_ELEM(6);
+        FP_ELEM(7);
+        FP_ELEM(8);
+        FP_ELEM(9);
+        FP_ELEM(10);
+        FP_ELEM(11);
+        FP_ELEM(12);
+        FP_ELEM(13);
+        FP_ELEM(14);
+        FP_ELEM(15);
+        FP_ELEM(16);
+        default: break;
     }
-    k_bbox<<<E, kWave, 2 * V * sizeof(double), s>>>(h->geom, n1, h->d_binv, h->bbox, h->esize);
+#undef FP_ELEM
     FP_HIP(hipGetLastError());
-    k_obb<<<E, kWave, 2 * V * sizeof(double), s>>>(h->geom, n1, h->d_binv, h->bbox, h->esize,
-                                                    h->tol, h->obb);
+    SetupRead *rd = h->h_read;
+    k_gbox<<<1, 1024, 0, s>>>(h->bbox, E, bad, rd);
     FP_HIP(hipGetLastError());
-    k_erec<<<(E + 255) / 256, 256, 0, s>>>(h->bbox, h->obb, E, h->erec);
-    FP_HIP(hipGetLastError());
-    k_gbox<<<1, 256, 0, s>>>(h->bbox, E, h->d_g);
-    FP_HIP(hipGetLastError());
-    double gb[6];
-    int bad = 0;
-    FP_HIP(hipMemcpyAsync(gb, h->d_g, sizeof gb, hipMemcpyDeviceToHost, s));
-    FP_HIP(hipMemcpyAsync(&bad, h->d_flag, sizeof bad, hipMemcpyDeviceToHost, s));
     FP_HIP(hipStreamSynchronize(s));
-    if (bad) {
+    if (rd->bad) {
         set_error(std::string(who) + ": non-finite node coordinates");
         return FP_EINVAL;
     }
@@ -633,8 +657,8 @@ static int build_geometry(fp_handle *h, const double *x, const double *y, const 
     Grid g{};
     double ext[3], vol = 1.0;
     for (int a = 0; a < 3; ++a) {
-        g.lo[a] = gb[2 * a];
-        g.hi[a] = gb[2 * a + 1];
+        g.lo[a] = rd->box[2 * a];
+        g.hi[a] = rd->box[2 * a + 1];
         ext[a] = g.hi[a] - g.lo[a];
         if (!(ext[a] > 0.0)) ext[a] = 1e-300;
         vol *= ext[a];
@@ -661,41 +685,44 @@ static int build_geometry(fp_handle *h, const double *x, const double *y, const 
         FP_HIP(dalloc(h, &h->scan_tmp, h->scan_tmp_n));
     }
     int *cnt = h->cell_cnt;
+    const int eb = (E + 256 / kWave - 1) / (256 / kWave);
     FP_HIP(fill_int(cnt, 0, h->ncell + 1, s));
-    const int eb = (E + 255) / 256;
-    k_hash_pass<<<eb, 256, 0, s>>>(h->bbox, E, g, 0, cnt, nullptr, nullptr);
+    k_hash_pass<<<eb, 256, 0, s>>>(h->bbox, E, g, 0, cnt, nullptr, nullptr, 0);
     FP_HIP(hipGetLastError());
     FP_HIP(scan_exclusive(cnt, h->cell_off, (int)h->ncell, h->scan_tmp, s));
-    int nnz = 0;
-    FP_HIP(hipMemcpyAsync(&nnz, h->cell_off + h->ncell, sizeof(int), hipMemcpyDeviceToHost, s));
-    FP_HIP(hipStreamSynchronize(s));
-    h->nnz = nnz;
-    if (nnz > h->nnz_cap || !h->cell_el) {
+    // lists in the room there is (kernels that find it too small do nothing)
+    for (int turn = 0; turn < 2; ++turn) {
+        int nblk = 0;
+        if (h->cell_el) {
+            k_hash_pass<<<eb, 256, 0, s>>>(h->bbox, E, g, 1, cnt, h->cell_off, h->cell_raw,
+                                           h->nnz_cap);
+            FP_HIP(hipGetLastError());
+            // (one counter per block: no more blocks than cells)
+            nblk = (int)std::max(1LL, std::min({(h->nnz_cap + 255) / 256, 4096LL, h->ncell}));
+            k_hash_place<<<nblk, 256, 0, s>>>(h->bbox, h->cell_off, h->ncell, h->cell_raw,
+                                              h->nnz_cap, h->cell_el, h->cell_box, cnt);
+            FP_HIP(hipGetLastError());
+        }
+        k_hash_read<<<1, kWave, 0, s>>>(h->cell_off, h->ncell, cnt, nblk, rd);
+        FP_HIP(hipGetLastError());
+        FP_HIP(hipStreamSynchronize(s));
+        h->nnz = rd->nnz;
+        if (h->cell_el && h->nnz <= h->nnz_cap) break;
         (void)hipFree(h->cell_el);
         (void)hipFree(h->cell_box);
-        h->bytes -= (sizeof(int) + 2 * sizeof(float4)) * (size_t)h->nnz_cap;
+        (void)hipFree(h->cell_raw);
+        h->bytes -= (sizeof(int) + 2 * sizeof(float4) + sizeof(int2)) * (size_t)h->nnz_cap;
         h->cell_el = nullptr;
         h->cell_box = nullptr;
-        h->nnz_cap = nnz;
-        FP_HIP(dalloc(h, &h->cell_el, (size_t)nnz));
-        FP_HIP(dalloc(h, &h->cell_box, 2 * (size_t)nnz));
+        h->cell_raw = nullptr;
+        h->nnz_cap = 0;
+        FP_HIP(dalloc(h, &h->cell_el, (size_t)h->nnz));
+        FP_HIP(dalloc(h, &h->cell_box, 2 * (size_t)h->nnz));
+        FP_HIP(dalloc(h, &h->cell_raw, (size_t)h->nnz));
+        h->nnz_cap = h->nnz;
     }
-    FP_HIP(fill_int(cnt, 0, h->ncell, s));
-    k_hash_pass<<<eb, 256, 0, s>>>(h->bbox, E, g, 1, cnt, h->cell_off, h->cell_el);
-    FP_HIP(hipGetLastError());
-    FP_HIP(hipMemsetAsync(h->d_flag, 0, sizeof(int), s));
-    k_hash_sort<<<(int)((h->ncell + 255) / 256), 256, 0, s>>>(h->cell_off, h->cell_el, h->ncell,
-                                                              h->d_flag);
-    FP_HIP(hipGetLastError());
-    int maxlen = 0;
-    FP_HIP(hipMemcpyAsync(&maxlen, h->d_flag, sizeof(int), hipMemcpyDeviceToHost, s));
-    FP_HIP(hipStreamSynchronize(s));
-    h->max_cell = maxlen;
-    if (nnz > 0) {
-        k_cellbox<<<(int)((nnz + 255) / 256), 256, 0, s>>>(h->bbox, h->cell_el, nnz, h->cell_box);
-        FP_HIP(hipGetLastError());
-    }
-    h->MC = std::max(1, maxlen);
+    h->max_cell = rd->maxlen;
+    h->MC = std::max(1, h->max_cell);
     return FP_OK;
 }
 
@@ -784,16 +811,15 @@ extern "C" int findpts_setup(fp_handle **out, const double *x, const double *y,
 
     // mesh-size arrays (kept for the handle's lifetime)
     FP_HIP_H(dalloc(h, &h->geom, 3 * EV));
-    FP_HIP_H(dalloc(h, &h->geom32, 3 * EV));  // kept for either precision
     FP_HIP_H(dalloc(h, &h->esize, E));
     FP_HIP_H(dalloc(h, &h->bbox, 6 * (size_t)E));
-    FP_HIP_H(dalloc(h, &h->obb, 18 * (size_t)E));
     FP_HIP_H(dalloc(h, &h->erec, 16 * (size_t)E));
     FP_HIP_H(dalloc(h, &h->stats, kStats));
     FP_HIP_H(dalloc(h, &h->d_basis, 2 * kMaxN1));
     FP_HIP_H(dalloc(h, &h->d_basis32, 2 * kMaxN1));
     FP_HIP_H(dalloc(h, &h->d_flag, 1));
-    FP_HIP_H(dalloc(h, &h->d_g, 6));
+    FP_HIP_H(hipHostMalloc((void **)&h->h_read, sizeof(SetupRead), hipHostMallocDefault));
+    FP_HIP_H(fill_int(h->d_flag, 0, 1, s));
     FP_HIP_H(dalloc(h, &h->d_binv, (size_t)(n1 * n1)));
     FP_HIP_H(dalloc(h, &h->d_dnode, (size_t)(n1 * n1)));
     FP_HIP_H(hipMemcpyAsync(h->d_basis, &h->basis, sizeof(Basis), hipMemcpyHostToDevice, s));

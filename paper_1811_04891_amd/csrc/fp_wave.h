@@ -50,6 +50,26 @@ __device__ __forceinline__ void wave_sum4(double &a, double &b, double &c, doubl
     d = read_lane(u, 48);
 }
 
+// Minima over the 64 lanes of four values, in every lane (and wave-uniform).
+__device__ __forceinline__ void wave_min4(double &a, double &b, double &c, double &d)
+{
+    double x, y;
+    swap2<32>(a, c, x, y);
+    const double s = fmin(x, y);
+    swap2<32>(b, d, x, y);
+    const double t = fmin(x, y);
+    swap2<16>(s, t, x, y);
+    double u = fmin(x, y);
+    u = fmin(u, row_ror<8>(u));
+    u = fmin(u, row_ror<4>(u));
+    u = fmin(u, row_ror<2>(u));
+    u = fmin(u, row_ror<1>(u));
+    a = read_lane(u, 0);
+    b = read_lane(u, 16);
+    c = read_lane(u, 32);
+    d = read_lane(u, 48);
+}
+
 // Lane l owns the node rows (j, k) = l, l + 64, ... of an element.
 template <int N1>
 struct WaveShape {
