@@ -429,6 +429,22 @@ __device__ __forceinline__ double node_dist2(double t0, double t1, double t2)
     return (t0 * t0 + t1 * t1) + t2 * t2;
 }
 
+// Slot and point of one pair of a unit's list, loaded ahead of the element's
+// staging so that the two chains of loads (list, then point) overlap it.
+struct PairAhead {
+    int slot = 0;
+    double x[3] = {0.0, 0.0, 0.0};
+    __device__ __forceinline__ void load(const LocArgs &a, int q, int end)
+    {
+        if (q >= end) return;
+        slot = a.order[q];
+        const double *p = a.pts + 3 * (long long)(slot % a.M);
+        x[0] = p[0];
+        x[1] = p[1];
+        x[2] = p[2];
+    }
+};
+
 // Reference coordinates of GLL node n (i + n1 (j + n1 k)).
 template <int N1>
 __device__ __forceinline__ void node_rst(BasisPtr<double> B, int n, double (&r)[3])
