@@ -100,3 +100,42 @@ def test_small_call_sessions_and_field_counts(N, nf):
     hf = [f.numpy() for f in fields]
     compare_eval(out, om.eval(res[0], res[1], res[2], hf), hf)
     h.free()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("N", [2, 5, 7, 9, 12])
+def test_grouped_call_sessions(N, prec):
+    """A call past the limit on three sessions (two annuli that overlap, and a
+    third that covers part of both): untagged points in two or three meshes go
+    to the largest distance field."""
+    from paper_1811_04891_amd import findpts as fp
+    print(f"case: grouped call, three sessions, order {N}, {prec}", flush=True)
+    dev = torch.device("cuda:0")
+    ms = [w.annulus_mesh(2, 10, 2, 0.5, 0.8, N=N), w.annulus_mesh(2, 12, 3, 0.7, 1.0, N=N),
+          w.annulus_mesh(1, 11, 2, 0.6, 0.9, N=N)]
+    x, y, z = (torch.cat([getattr(m, c) for m in ms]) for c in "xyz")
+    sess = torch.cat([torch.full((m.E,), i, dtype=torch.int32) for i, m in enumerate(ms)])
+    rho = torch.sqrt(x * x + y * y)
+    s = sess[:, None, None, None]
+    delta = torch.where(s == 0, 0.8 - rho, torch.where(s == 1, rho - 0.7, 0.08 - 0.4 * rho * rho / 4))
+    delta = delta.contiguous()
+    mesh = w.Mesh("three", N, x, y, z, sess, delta)
+    n = LIMIT + 321
+    pts = _points(n, 7)
+    tags = torch.as_tensor((np.arange(n) % 4 - 1).astype(np.int32))
+    md = mesh.to(dev)
+    h = fp.findpts_setup(md.x, md.y, md.z, N, tol=TOL, elem_session=md.session, delta=md.delta,
+                         max_points=n, precision=fp.FP_PREC_MIXED if prec == "mixed"
+                         else fp.FP_PREC_FP64)
+    code, el, rst, d2 = fp.findpts(h, torch.as_tensor(pts).to(dev), tags.to(dev))
+    torch.cuda.synchronize()
+    res = [t.cpu().numpy() for t in (code, el, rst, d2)]
+    om = oracle.OracleMesh.from_mesh(mesh, TOL)
+    _, hs = om.bbox()
+    sub = np.arange(0, n, 8)
+    ref = om.findpts(pts[sub], tags.numpy()[sub])
+    st = compare_locate(om, pts[sub], [a[sub] for a in res], ref, hs, TOL)
+    assert st["inside"] > 1000
+    own = sess.numpy()[res[1][res[0] == 0]]
+    assert np.all(np.bincount(own, minlength=3) > 100)
+    h.free()
