@@ -289,28 +289,4 @@ __device__ __forceinline__ void geo_value(cptr<T> X, BasisPtr<T> B,
     for (int c = 0; c < 3; ++c) x[c] = v[c];
 }
 
-// Scalar field value at r given the basis values.
-template <int N1>
-__device__ __forceinline__ double field_value(cptr<double> F,
-                                              const double (&hr)[N1], const double (&hs)[N1],
-                                              const double (&ht)[N1])
-{
-    double v = 0.0;
-#pragma unroll Unroll<N1>::jk
-    for (int k = 0; k < N1; ++k) {
-        double cs = 0.0;
-#pragma unroll Unroll<N1>::jk
-        for (int j = 0; j < N1; ++j) {
-            double a = 0.0;
-            const int row = N1 * (j + N1 * k);
-            FP_PIN_SGPR(F);
-#pragma unroll
-            for (int i = 0; i < N1; ++i) a = fma(F[row + i], hr[i], a);
-            cs = fma(a, hs[j], cs);
-        }
-        v = fma(cs, ht[k], v);
-    }
-    return v;
-}
-
 }  // namespace fp

@@ -121,113 +121,6 @@ static void launch_unstage(const EvArgs &a, int nblk, hipStream_t s)
     }
 }
 
-// One wavefront per work unit: up to kUnitEval points of one element, 64 at a
-// time, field rows through scalar loads.
-constexpr int kUnitEval = 256;
-
-template <int N1>
-__global__ __launch_bounds__(kWave) void k_eval(EvArgs a, FieldPtrs F, const double *__restrict__ basis)
-{
-    constexpr int V = N1 * N1 * N1;
-    const BasisPtr<double> B{as_const(basis)};
-    const UnitList units(a.off, a.E, 1, a.E, kUnitEval);
-    for (long long unit = xcd_unit(blockIdx.x, gridDim.x); unit < units.end; unit += gridDim.x) {
-        Unit U;
-        if (!units.at(unit, U)) continue;
-        const int e = U.seg, beg = U.beg, end = U.end;
-        for (int base = beg; base < end; base += kWave) {
-            const int q = base + (int)threadIdx.x;
-            const bool act = q < end;
-            const int p = act ? a.order[q] : 0;
-            double r0 = 0.0, r1 = 0.0, r2 = 0.0;
-            if (act) {
-                r0 = a.rst[3 * (long long)p];
-                r1 = a.rst[3 * (long long)p + 1];
-                r2 = a.rst[3 * (long long)p + 2];
-            }
-            double hr[N1], hs[N1], ht[N1];
-            lagrange<N1>(B, r0, hr);
-            lagrange<N1>(B, r1, hs);
-            lagrange<N1>(B, r2, ht);
-            for (int f = 0; f < a.nf; ++f) {
-                const double v = field_value<N1>(as_const(F.f[f] + (long long)e * V), hr, hs, ht);
-                if (act) a.out[f * a.ostride + p] = v;
-            }
-        }
-    }
-}
-
-// Field rows of one staged element: value-only contraction, r then s then t.
-template <int N1>
-struct FieldAcc {
-    double hr[N1], hs[N1], ht[N1];
-    double v, cs;
-    template <int c, int j, int k>
-    __device__ __forceinline__ void step(const double (&row)[N1])
-    {
-        double a = 0.0;
-#pragma unroll
-        for (int i = 0; i < N1; ++i) a = fma(row[i], hr[i], a);
-        cs = (j == 0) ? a * hs[0] : fma(a, hs[j], cs);
-        if constexpr (j == N1 - 1) v = (k == 0) ? cs * ht[0] : fma(cs, ht[k], v);
-    }
-};
-
-// Element groups staged in LDS, one field at a time.  A 256-thread block
-// takes a work unit: G consecutive elements and a run of up to kUnitGrp of
-// their points (contiguous in the element-grouped order); for each field it stages the G element blocks
-// (padded by 16 bytes so lanes on different elements use different LDS
-// banks) and every thread interpolates its points.
-constexpr int kEvThreads = 256;
-constexpr int kUnitGrp = 1024;  // points of one element group per work unit
-
-template <int N1>
-struct EvGroup {
-    static constexpr int V = N1 * N1 * N1;
-    static constexpr int stride = V + 2;
-    static constexpr int G0 = (6 * 8192) / (stride * 8);
-    static constexpr int G = G0 < 1 ? 1 : (G0 > 32 ? 32 : G0);
-};
-
-template <int N1>
-__global__ __launch_bounds__(kEvThreads) void k_eval_grp(EvArgs a, FieldPtrs F,
-                                                         const double *__restrict__ basis)
-{
-    using Gr = EvGroup<N1>;
-    constexpr int V = Gr::V, G = Gr::G, S = Gr::stride;
-    __shared__ double sF[G * S];
-    const BasisPtr<double> B{as_const(basis)};
-    const int ns = (a.E + G - 1) / G;
-    const UnitList units(a.off, ns, G, a.E, kUnitGrp);
-    for (long long unit = xcd_unit(blockIdx.x, gridDim.x); unit < units.end; unit += gridDim.x) {
-        Unit U;
-        if (!units.at(unit, U)) continue;  // uniform
-        const int e0 = U.seg * G;
-        const int ne = min(G, a.E - e0);
-        const int pb = U.beg, pe = U.end;
-        for (int f = 0; f < a.nf; ++f) {
-            const double *src = F.f[f] + (long long)e0 * V;
-            for (int q = threadIdx.x; q < ne * V; q += kEvThreads) {
-                const int g = q / V;
-                sF[g * S + (q - g * V)] = src[q];
-            }
-            __syncthreads();
-            for (int u = pb + threadIdx.x; u < pe; u += kEvThreads) {
-                const int p = a.order[u];
-                const int g = a.el[p] - e0;
-                FieldAcc<N1> acc;
-                lagrange<N1>(B, a.rst[3 * (long long)p], acc.hr);
-                lagrange<N1>(B, a.rst[3 * (long long)p + 1], acc.hs);
-                lagrange<N1>(B, a.rst[3 * (long long)p + 2], acc.ht);
-                double buf[kPrefetch + 1][N1];
-                walk_rows<N1, 1, 0>((lptr<double>)(sF + g * S), buf, acc);
-                a.out[f * a.ostride + p] = acc.v;
-            }
-            __syncthreads();
-        }
-    }
-}
-
 // Interpolation on the matrix cores (orders 1..7): one wavefront per work
 // unit (up to kUnitEvalMfma points of one element), points in batches of 16.
 // For field f the first contraction a_f(k, j; point) = sum_i F_f[k][j][i]
@@ -275,7 +168,7 @@ void k_eval_mfma(EvArgs a, FieldPtrs F,
         Unit U;
         if (!units.at(unit, U)) continue;
         const int e = U.seg, beg = U.beg, end = U.end;
-        const int lane = threadIdx.x, n = lane & 15, g = lane >> 4;
+        const int lane = threadIdx.x, n = lane & 15;
         // A fragment coordinates of this lane: row -> plane p, row jj; column i
         const int row = lane & 15, q = lane >> 4;
         const int gr = MF<T>::grp(row), vr = MF<T>::comp(row);
@@ -371,6 +264,134 @@ void k_eval_mfma(EvArgs a, FieldPtrs F,
                 }
                 v = slot_sum(v);
                 dst[act ? f * fs : 0] = (double)v;
+            }
+        }
+    }
+}
+
+// Interpolation on the matrix cores at orders 8 to 15: one wavefront per work
+// unit (up to kUnitEvalPl points of one element), binary64.  As k_eval_mfma,
+// with the rows laid out one plane per lane: the rows of tile (m, hj) are the
+// node rows j = 4 hj + v of the planes k = 4 m + g, so lane g of a point
+// contracts whole planes with h_j(s) and weights them with its own h_k(t), and
+// needs r and t basis values only at the indices 4 m + g.  An element's fragments
+// do not fit in registers (27 to 64 per lane and field): they are read from
+// memory, one plane group at a time with the next one's loads in flight, for
+// one or two batches of 16 points whose basis values stay in registers through all the
+// fields.  Fragments past the last node are zeroed (a field may hold any
+// value, so a zero weight would not do).
+//
+// What bounds it: the fragments' reads (16 pieces of 32 bytes each, through the
+// first-level cache) and the matrix products, 64 cycles per 16 rows x 4 x 16
+// points, a third to four ninths of them padding at 9, 10 and 13 nodes per
+// direction.  Measured against the kernels it replaces: 2e6 points on 20,000
+// elements of order 9, 4 fields, 0.95 -> 0.84 ms (every node value of a point
+// came from LDS); 1.5e5 points on 46,656 elements, 3 fields, 0.58 -> 0.35 ms
+// (the elements' values alone are 1.1 GB); 2e5 points on 2,048 elements of order
+// 12, 2 fields, 0.32 -> 0.13 ms (node values through scalar loads).  Units of 128
+// or 256 points, three batches per read and staged output: within 3 %.
+constexpr int kUnitEvalPl = 64;  // points of one element per work unit
+// Batches of 16 points that share a read of the fragments (two spill 110 to 190
+// bytes above 12 nodes per direction).
+template <int N1>
+constexpr int kEvalBatches = N1 <= 12 ? 2 : 1;
+
+template <int N1>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2))) void k_eval_pl(
+    EvArgs a, FieldPtrs F, const double *__restrict__ basis)
+{
+    constexpr int V = N1 * N1 * N1, Q = (N1 + 3) / 4, BT = kEvalBatches<N1>;
+    const BasisPtr<double> B{as_const(basis)};
+    // lane-rotated node tables of the 4 lane groups, read at every batch
+    // instead of being held in registers
+    __shared__ LaneNodes<N1> sZ[4];
+    const int lane = threadIdx.x, n = lane & 15, g = lane >> 4;
+    if (lane < 4) lane_nodes<N1>(B, lane, sZ[lane]);
+    __syncthreads();
+    // this lane's fragment: row 4 v + g (plane g, node row v of a tile), column q
+    const int rg = n & 3, rv = n >> 2;
+    const int off = N1 * (rv + N1 * rg) + g;
+    const UnitList units(a.off, a.E, 1, a.E, kUnitEvalPl);
+    for (long long unit = xcd_unit(blockIdx.x, gridDim.x); unit < units.end; unit += gridDim.x) {
+        Unit U;
+        if (!units.at(unit, U)) continue;
+        for (int c0 = U.beg; c0 < U.end; c0 += 16 * BT) {
+            double hr[BT][Q], hs[BT][N1], ht[BT][Q];
+            int p[BT], sl[BT];
+            bool act[BT];
+#pragma unroll
+            for (int b = 0; b < BT; ++b) {
+                const int u = c0 + 16 * b + n;
+                act[b] = u < U.end;
+                p[b] = a.order[act[b] ? u : U.beg];
+                sl[b] = a.slot[act[b] ? u : U.beg];
+            }
+            double r[BT][3];
+#pragma unroll
+            for (int b = 0; b < BT; ++b)
+#pragma unroll
+                for (int d = 0; d < 3; ++d) r[b][d] = a.rst[3 * (long long)p[b] + d];
+#pragma unroll
+            for (int b = 0; b < BT; ++b) {
+                const LaneNodes<N1> *zp = sZ + g;
+                asm volatile("" : "+v"(zp));  // read per batch, not hoisted
+                const LaneNodes<N1> Z = *zp;
+                lagrange_lane<N1>(Z, r[b][0], hr[b]);
+                lagrange<N1>(B, r[b][1], hs[b]);
+                lagrange_lane<N1>(Z, r[b][2], ht[b]);
+            }
+            const bool two = c0 + 16 < U.end;  // the second batch holds points
+            const long long fs = a.stage ? 1 : a.ostride;
+            for (int f = 0; f < a.nf; ++f) {
+                const double *src = F.f[f] + (long long)U.seg * V;
+                const auto frags = [&](int m, double (&A)[Q][Q]) {
+#pragma unroll
+                    for (int hj = 0; hj < Q; ++hj)
+#pragma unroll
+                        for (int kb = 0; kb < Q; ++kb) {
+                            const int k = 4 * m + rg, j = 4 * hj + rv, i = 4 * kb + g;
+                            const bool ok = (4 * m + 3 < N1 || k < N1) &&
+                                            (4 * hj + 3 < N1 || j < N1) &&
+                                            (4 * kb + 3 < N1 || i < N1);
+                            const double v = src[ok ? off + 4 * N1 * N1 * m + 4 * N1 * hj + 4 * kb : 0];
+                            A[hj][kb] = ok ? v : 0.0;
+                        }
+                };
+                double v[BT];
+#pragma unroll
+                for (int b = 0; b < BT; ++b) v[b] = 0.0;
+                double A[2][Q][Q];
+                frags(0, A[0]);
+#pragma unroll
+                for (int m = 0; m < Q; ++m) {
+                    if (m + 1 < Q) frags(m + 1, A[(m + 1) & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int b = 0; b < BT; ++b) {
+                        if (b == 0 || two) {
+                            // neighbouring products are independent
+                            dx4 c[Q];
+#pragma unroll
+                            for (int kb = 0; kb < Q; ++kb)
+#pragma unroll
+                                for (int hj = 0; hj < Q; ++hj) {
+                                    const dx4 z = {0, 0, 0, 0};
+                                    c[hj] = MF<double>::mma(A[m & 1][hj][kb], hr[b][kb],
+                                                            kb == 0 ? z : c[hj]);
+                                }
+                            double sa = 0.0;
+#pragma unroll
+                            for (int j = 0; j < N1; ++j) sa = fma(c[j / 4][j % 4], hs[b][j], sa);
+                            v[b] = fma(sa, ht[b][m], v[b]);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int b = 0; b < BT; ++b) {
+                    const double s = slot_sum(v[b]);
+                    if (act[b] && g == 0)
+                        (a.stage ? a.stage + (long long)sl[b] * a.nf : a.out + p[b])[f * fs] = s;
+                }
             }
         }
     }
@@ -480,35 +501,22 @@ static hipError_t launch_eval_kernel(int n1, int E, int n, const EvArgs &a, cons
 #undef FP_LAUNCH_MFMA
 #undef FP_EVAL_NF
 #undef FP_EVAL_MFMA
-#define FP_LAUNCH_GRP(N1)                                                                 \
-    k_eval_grp<N1><<<unit_grid((E + EvGroup<N1>::G - 1) / EvGroup<N1>::G, n, kUnitGrp),   \
-                     kEvThreads, 0, s>>>(a, F, B)
+#define FP_LAUNCH_PL(N1)                                                             \
+    case N1:                                                                         \
+        k_eval_pl<N1><<<unit_grid(E, n, kUnitEvalPl), kWave, 0, s>>>(a, F, B);       \
+        break
     switch (n1) {
-        case 9: FP_LAUNCH_GRP(9); return hipGetLastError();
-        case 10: FP_LAUNCH_GRP(10); return hipGetLastError();
-        default: break;
-    }
-#undef FP_LAUNCH_GRP
-#define FP_LAUNCH_EVAL(N1) k_eval<N1><<<unit_grid(E, n, kUnitEval), kWave, 0, s>>>(a, F, B)
-    switch (n1) {
-        case 2: FP_LAUNCH_EVAL(2); break;
-        case 3: FP_LAUNCH_EVAL(3); break;
-        case 4: FP_LAUNCH_EVAL(4); break;
-        case 5: FP_LAUNCH_EVAL(5); break;
-        case 6: FP_LAUNCH_EVAL(6); break;
-        case 7: FP_LAUNCH_EVAL(7); break;
-        case 8: FP_LAUNCH_EVAL(8); break;
-        case 9: FP_LAUNCH_EVAL(9); break;
-        case 10: FP_LAUNCH_EVAL(10); break;
-        case 11: FP_LAUNCH_EVAL(11); break;
-        case 12: FP_LAUNCH_EVAL(12); break;
-        case 13: FP_LAUNCH_EVAL(13); break;
-        case 14: FP_LAUNCH_EVAL(14); break;
-        case 15: FP_LAUNCH_EVAL(15); break;
-        case 16: FP_LAUNCH_EVAL(16); break;
+        FP_LAUNCH_PL(9);
+        FP_LAUNCH_PL(10);
+        FP_LAUNCH_PL(11);
+        FP_LAUNCH_PL(12);
+        FP_LAUNCH_PL(13);
+        FP_LAUNCH_PL(14);
+        FP_LAUNCH_PL(15);
+        FP_LAUNCH_PL(16);
         default: return hipErrorInvalidValue;
     }
-#undef FP_LAUNCH_EVAL
+#undef FP_LAUNCH_PL
     return hipGetLastError();
 }
 
