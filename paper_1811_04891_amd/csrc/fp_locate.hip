@@ -14,8 +14,8 @@
 //   k_locate_mfma  (orders 1..7) one wavefront per work unit (a run of one
 //              element's pairs), element block in LDS, map and Jacobian of 16
 //              pairs at a time on the matrix cores (fp_mfma.inc)
-//   k_locate   (orders 8..15) one wavefront per work unit of 64 pairs,
-//              lanes = pairs, node rows through scalar loads
+//   k_newton_pl  (orders 8..15) blocks of wavefronts per work unit, the element
+//              in LDS, matrix cores (fp_newton_pl.inc)
 //   k_select   per point: classification and owner rule, caller's order
 #include <algorithm>
 #include <cmath>
@@ -63,6 +63,7 @@ struct LocArgs {
     int pair_max;         // second pass: up to this many pairs run on k_newton_pair
                           // (one wavefront per pair)
     unsigned *pt_part;    // small calls: counters of each block
+    int unit;             // orders 8 to 15: pairs per work unit
 };
 
 __device__ __forceinline__ int cell_of(const Grid &g, int a, double x)
@@ -471,104 +472,6 @@ __device__ __forceinline__ void store_pair(const LocArgs &a, int slot, const TRN
     a.res_in[slot] = sqrt(t.phi) <= a.tol * he ? 1 : 0;
 }
 
-// One 64-lane wavefront per work unit (up to 64 pairs of one element), lanes
-// over its pairs, node rows from the scalar cache (orders 8 and above, whose
-// matrix-core fragments would not fit in registers).
-constexpr int kUnitScalar = 64;
-
-// Map and Jacobian at GLL node nd of an element in global memory: the value
-// is the node itself, each derivative a one-dimensional sum along its line
-// (D = h_b'(z_a) at a n1 + b).
-template <int N1>
-__device__ __forceinline__ void node_geo_g(const double *__restrict__ X,
-                                           const double *__restrict__ D, int nd,
-                                           double (&x)[3], double (&J)[9])
-{
-    constexpr int V = N1 * N1 * N1;
-    const int i0 = nd % N1, j0 = (nd / N1) % N1, k0 = nd / (N1 * N1);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const double *Xc = X + c * V;
-        double dr = 0.0, ds = 0.0, dt = 0.0;
-#pragma unroll
-        for (int m = 0; m < N1; ++m) {
-            dr = fma(Xc[nd - i0 + m], D[i0 * N1 + m], dr);
-            ds = fma(Xc[nd + N1 * (m - j0)], D[j0 * N1 + m], ds);
-            dt = fma(Xc[nd + N1 * N1 * (m - k0)], D[k0 * N1 + m], dt);
-        }
-        x[c] = Xc[nd];
-        J[3 * c] = dr;
-        J[3 * c + 1] = ds;
-        J[3 * c + 2] = dt;
-    }
-}
-
-template <int N1>
-__global__ __launch_bounds__(kWave) void k_locate(LocArgs a, const double *__restrict__ basis,
-                                                  const double *__restrict__ dnode)
-{
-    if (a.only && !*a.gate) return;
-    // a short second pass runs on k_newton_pair
-    if (a.only && a.elem_off[a.E] <= a.pair_max) return;
-    constexpr int V = N1 * N1 * N1;
-    const BasisPtr<double> B{as_const(basis)};
-    unsigned long long my_iters = 0;
-    const UnitList units(a.elem_off, a.E, 1, a.E, kUnitScalar);
-    for (long long u = xcd_unit(blockIdx.x, gridDim.x); u < units.end; u += gridDim.x) {
-        Unit U;
-        if (!units.at(u, U)) continue;
-        const int e = U.seg;
-        cptr<double> X = as_const(a.geom + (long long)e * 3 * V);
-        const double he = a.esize[e];
-        const double rstop = resid_stop(a.tol, he);
-        const int q = U.beg + (int)threadIdx.x;
-        const bool act = q < U.end;
-        const int slot = act ? a.order[q] : 0;
-        const int p = slot % a.M;
-        double xs[3] = {0.0, 0.0, 0.0};
-        if (act) {
-            xs[0] = a.pts[3 * (long long)p];
-            xs[1] = a.pts[3 * (long long)p + 1];
-            xs[2] = a.pts[3 * (long long)p + 2];
-        }
-        // closest mapped GLL node (ties: smallest node index)
-        double best = INFINITY;
-        int bq = 0;
-#pragma unroll 8
-        for (int n = 0; n < V; ++n) {
-            const double d = node_dist2(X[n] - xs[0], X[V + n] - xs[1], X[2 * V + n] - xs[2]);
-            if (d < best) {
-                best = d;
-                bq = n;
-            }
-        }
-        double r0[3];
-        node_rst<N1>(B, bq, r0);
-        TRNewton t;
-        t.start(r0);
-        // the first Newton step from the node's own value and line sums
-        bool done = !act;
-        if (act) {
-            double xn[3], Jn[9];
-            node_geo_g<N1>(a.geom + (long long)e * 3 * V, dnode, bq, xn, Jn);
-            done = t.update(xn, Jn, xs, rstop);
-        }
-        while (!done) {
-            double xt[3], Jt[9];
-            geo_eval<N1>(X, B, t.rt, xt, Jt);
-            done = t.update(xt, Jt, xs, rstop);
-        }
-        if (act) {
-            my_iters += (unsigned long long)t.it;
-            store_pair(a, slot, t, he);
-        }
-    }
-    // wave totals -> counters
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) my_iters += __shfl_xor(my_iters, o, kWave);
-    if (threadIdx.x == 0) a.iter_part[blockIdx.x] = (unsigned)my_iters;
-}
-
 #include "fp_mfma.inc"
 #include "fp_start.inc"
 #include "fp_newton8.inc"
@@ -797,9 +700,22 @@ __global__ __launch_bounds__(256) void k_select(LocArgs a, const double *__restr
         default: return hipErrorInvalidValue; \
     }
 
+// Orders 8 and 9 have a binary32 phase.
+constexpr int kMixedPlMaxN1 = 10;
+
+// Pairs per work unit of the kernels of orders 8 to 15 for n points on E
+// elements: kUnitPl, or as few as one batch per wavefront (step pairs) where
+// the elements alone do not make 2,048 units.
+static int unit_pl(int E, int n, int step)
+{
+    if (E >= 2048) return kUnitPl;
+    const int k = (n / 2048 + step - 1) / step * step;
+    return std::min(std::max(k, std::max(step, kUnitMin)), kUnitPl);
+}
+
 // Launches the order's Newton kernel over the work units of the pass's pairs
 // (n points); *nblk receives the grid size (one iteration partial per block).
-static hipError_t launch_locate_kernel(const fp_handle *h, const LocArgs &a, int n,
+static hipError_t launch_locate_kernel(const fp_handle *h, LocArgs a, int n,
                                        hipStream_t s, int *nblk)
 {
 #define FP_GRID(K) (a.only ? std::min(unit_grid(h->E, n, (K)), kSecondPassGrid) \
@@ -812,12 +728,6 @@ static hipError_t launch_locate_kernel(const fp_handle *h, const LocArgs &a, int
         } else {                                                            \
             if (a.only) k_newton_pair_rows<N1><<<*nblk, kWave, 0, s>>>(a, h->d_basis); \
         }                                                                   \
-    } while (0)
-#define FP_LAUNCH_LOCATE(N1)                                      \
-    do {                                                          \
-        *nblk = FP_GRID(kUnitScalar);                             \
-        k_locate<N1><<<*nblk, kWave, 0, s>>>(a, h->d_basis, h->d_dnode); \
-        FP_LAUNCH_PAIR(N1);                                       \
     } while (0)
 // mixed precision: first pass only (the second pass is binary64).  At order 5
 // the binary64 kernel (two wavefronts per SIMD) is faster than the binary32
@@ -842,18 +752,25 @@ constexpr int kBinary64Only = 6;
         }                                                                            \
         FP_LAUNCH_PAIR(N1);                                                          \
     } while (0)
-// orders 8 and 9: matrix cores, one plane per lane; mixed precision (first
-// pass): a binary32 phase, then binary64 Newton from its end points
+// orders 8 to 15: matrix cores, one plane per lane; mixed precision at orders
+// 8 and 9 (first pass): a binary32 phase, then binary64 Newton from its end points
 #define FP_LAUNCH_PL(N1)                                                              \
     do {                                                                              \
-        *nblk = FP_GRID(kUnitPl);                                                     \
-        if (h->precision == FP_PREC_MIXED && a.first) {                                 \
-            k_mixed_pl<N1><<<*nblk, 2 * kWave, 0, s>>>(a, h->d_basis32, h->d_dnode); \
-            k_newton_pl<N1, true><<<*nblk, 2 * kWave, 0, s>>>(a, h->d_basis, h->d_basis32, \
-                                                             h->d_dnode);             \
-        } else                                                                        \
-            k_newton_pl<N1, false><<<*nblk, 2 * kWave, 0, s>>>(a, h->d_basis, h->d_basis32, \
-                                                              h->d_dnode);            \
+        constexpr int T = PLShape<N1>::T;                                             \
+        a.unit = unit_pl(h->E, n, 16 * PLShape<N1>::W);                               \
+        *nblk = FP_GRID(a.unit);                                                      \
+        bool done = false;                                                            \
+        if constexpr (N1 <= kMixedPlMaxN1) {                                          \
+            if (h->precision == FP_PREC_MIXED && a.first) {                           \
+                k_mixed_pl<N1><<<*nblk, T, 0, s>>>(a, h->d_basis32, h->d_dnode);      \
+                k_newton_pl<N1, true><<<*nblk, T, 0, s>>>(a, h->d_basis, h->d_basis32, \
+                                                          h->d_dnode);                \
+                done = true;                                                          \
+            }                                                                         \
+        }                                                                             \
+        if (!done)                                                                    \
+            k_newton_pl<N1, false><<<*nblk, T, 0, s>>>(a, h->d_basis, h->d_basis32,   \
+                                                       h->d_dnode);                   \
         FP_LAUNCH_PAIR(N1);                                                           \
     } while (0)
     switch (h->n1) {
@@ -866,15 +783,14 @@ constexpr int kBinary64Only = 6;
         case 8: FP_LAUNCH_MFMA(8); break;
         case 9: FP_LAUNCH_PL(9); break;
         case 10: FP_LAUNCH_PL(10); break;
-        case 11: FP_LAUNCH_LOCATE(11); break;
-        case 12: FP_LAUNCH_LOCATE(12); break;
-        case 13: FP_LAUNCH_LOCATE(13); break;
-        case 14: FP_LAUNCH_LOCATE(14); break;
-        case 15: FP_LAUNCH_LOCATE(15); break;
-        case 16: FP_LAUNCH_LOCATE(16); break;
+        case 11: FP_LAUNCH_PL(11); break;
+        case 12: FP_LAUNCH_PL(12); break;
+        case 13: FP_LAUNCH_PL(13); break;
+        case 14: FP_LAUNCH_PL(14); break;
+        case 15: FP_LAUNCH_PL(15); break;
+        case 16: FP_LAUNCH_PL(16); break;
         default: return hipErrorInvalidValue;
     }
-#undef FP_LAUNCH_LOCATE
 #undef FP_LAUNCH_PAIR
 #undef FP_LAUNCH_MFMA
 #undef FP_LAUNCH_PL
