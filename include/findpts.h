@@ -333,8 +333,9 @@ FP_API int fp_extrapolate(long long n, int order, const double *const *h_hist, d
  *     stream completes; waiting requests are then admitted.
  *   - Results equal those of findpts + findpts_eval on the request alone
  *     (every point's result depends only on that point, the mesh, and
- *     whether the call has at most 16,384 points: such calls run other
- *     kernels, whose results may differ by rounding).
+ *     whether the call is small: calls of at most 16,384 points, 4,096 to
+ *     8,192 at orders above 9, run other kernels, whose results may differ
+ *     by rounding).
  *   - Latency of a request = host time from fps_submit to the completion of
  *     its last kernel (a host callback on its stream).
  *

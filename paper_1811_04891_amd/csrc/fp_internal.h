@@ -322,16 +322,27 @@ hipError_t fill_int(int *p, int value, long long n, hipStream_t s);
 // by element (k_point, k_eval_point): decided by the call's size alone, so that
 // a call's results do not depend on how it is cut into passes.  The grouped
 // path costs a call of 1,000 points 92 to 238 us of findpts at orders 3 to 9
-// (about 20 launches and a chain of 16-slot rounds) against 30 to 52 us, and
-// 1.3 to 2.6 ms at orders 12 and 15 against 0.08 to 0.23; at kPointMax points
-// the two are level on meshes with a few points per element (order 3: 111
-// against 91 us; order 7: 173 against 116) and one wavefront per point still
-// takes half the time on crowded elements.  Interpolation: 28 to 280 us against
-// 15 to 24 at 1,000 points, level at kPointMax.  Mixed precision at the orders
-// that interpolate in binary32 stays on its own kernels at every size.
+// (about 20 launches and a chain of 16-slot rounds) against 30 to 52 us, and 250
+// to 500 us at orders 12 and 15 against 83 to 232.  At 16,000 points on 125 or
+// 2,048 elements it takes 110 to 235 us against 91 to 134 at orders 3 to 7, 270
+// to 350 against 227 to 267 at orders 9 and 10, 443 to 566 against 496 to 547
+// at order 12, but 533 to 851 against 866 to 875 at order 13 and 0.67 to 1.11
+// ms against 1.21 to 1.31 at order 15, which is level near 6,000.
+// Interpolation (of 2 fields): 27 to 28 us against 12 to 13 at 1,000 points; at
+// 16,000 points 36 to 41 against 20 to 34 at order 9; level near 8,000 points
+// at orders 10 to 12 and 4,000 above.  Mixed precision at the orders that
+// interpolate in binary32 stays on its own kernels at every size.
+inline bool point_path(const fp_handle *h)
+{
+    return !(h->precision == FP_PREC_MIXED && h->n1 <= kMixed32MaxN1);
+}
 inline bool small_call(const fp_handle *h, int npts)
 {
-    return npts <= kPointMax && !(h->precision == FP_PREC_MIXED && h->n1 <= kMixed32MaxN1);
+    return point_path(h) && npts <= (h->n1 <= 13 ? kPointMax : 6144);
+}
+inline bool small_eval(const fp_handle *h, int npts)
+{
+    return point_path(h) && npts <= (h->n1 <= 10 ? kPointMax : (h->n1 <= 13 ? 8192 : 4096));
 }
 
 // findpts / findpts_eval on a given workspace and stream (the public calls

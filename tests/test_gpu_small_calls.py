@@ -12,7 +12,8 @@ from parity import compare_eval, compare_locate
 pytestmark = pytest.mark.gpu
 
 TOL = 1e-12
-LIMIT = 16384  # kPointMax of the library
+LIMIT = 16384  # the largest call any order takes one wavefront per point
+SMALL = 4000   # every order does
 
 
 def _points(n, seed):
@@ -55,8 +56,9 @@ def test_both_paths_match_oracle(N):
     ref = om.findpts(pts[sub])
     hf = [f.numpy() for f in fields]
     compare_locate(om, pts[sub], [a[sub] for a in big], ref, hs, TOL)
+    cuts = [0, 1, 64] + list(range(64 + SMALL, n, SMALL)) + [n]
     parts = [_call(fp, h, dp[a:b].contiguous(), None, df)
-             for a, b in ((0, 1), (1, 64), (64, n))]
+             for a, b in zip(cuts[:-1], cuts[1:])]
     st = fp.findpts_stats(h)
     assert st[2] == n and st[3] == cands
     small = [np.concatenate([p[0][k] for p in parts]) for k in range(4)]
