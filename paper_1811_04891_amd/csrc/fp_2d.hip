@@ -28,6 +28,7 @@
 
 #include "fp_basis.h"
 #include "fp_internal.h"
+#include "fp_wave.h"
 
 struct fp2_handle {
     int device = 0;
@@ -57,6 +58,7 @@ struct fp2_handle {
     double *res_dl = nullptr;
     unsigned *iter_part = nullptr;
     unsigned *cand_part = nullptr;  // per k2_cand block: axis-aligned candidates
+    unsigned *pt_part = nullptr;    // small calls: counters of each k2_point block
     int *redo = nullptr;            // M: second-round flag per point
     int *ev_pos = nullptr, *ev_order = nullptr;
     int *scan_tmp = nullptr;
@@ -366,6 +368,7 @@ struct Loc2 {
     int *res_in;
     double *res_dl;
     unsigned *iter_part;
+    unsigned *pt_part;  // small calls: counters of each block
 };
 
 // Candidates of each point: hash cell, then the closed box, then session
@@ -592,6 +595,8 @@ struct TR2 {
         return ns <= kStepTiny2 || !(pred > 0.0);
     }
 };
+
+#include "fp_2d_point.inc"
 
 // One wavefront per work unit (up to 64 pairs of one element), one lane per
 // pair: closest mapped GLL node (ties: smallest node index), then Newton.
@@ -833,6 +838,31 @@ __global__ __launch_bounds__(256) void k2_ev_scatter(Ev2 a)
     if (k >= 0) a.order[a.off[a.el[p]] + k] = p;
 }
 
+// Small calls: 16 lanes per point, no grouping (as k2_point).
+template <int N1>
+__global__ __launch_bounds__(kWave) void k2_eval_point(Ev2 a, const double *__restrict__ basis)
+{
+    __shared__ double2 sh[kPoint2Groups][16];
+    const BasisPtr<double> B{as_const(basis)};
+    const int l = threadIdx.x & 15, gi = threadIdx.x >> 4;
+    Solver2<N1> P;
+    P.init(B, sh[gi], l);
+    for (int p = blockIdx.x * kPoint2Groups + gi; p < a.npts; p += gridDim.x * kPoint2Groups) {
+        const int e = a.el[p];
+        const bool ok = a.code[p] != FP_NOT_FOUND && e >= 0 && e < a.E;
+        if (ok) {
+            const double r[2] = {a.rs[2 * (long long)p], a.rs[2 * (long long)p + 1]};
+            const double2 hs = P.basis(r);
+            for (int f = 0; f < a.nf; ++f) {
+                const double v = P.field(a.f[f] + (long long)e * N1 * N1, hs);
+                if (l == 0) a.out[f * a.ostride + p] = v;
+            }
+        } else if (l < a.nf) {
+            a.out[l * a.ostride + p] = NAN;
+        }
+    }
+}
+
 constexpr int kUnitEval2 = 256;
 
 // One wavefront per work unit (up to 256 points of one element, 64 at a
@@ -897,6 +927,29 @@ hipError_t launch_locate2(const fp2_handle *h, const Loc2 &a, int nblk, hipStrea
 #define FP2_LOC(N1) k2_locate<N1><<<nblk, kWave, 0, s>>>(a, h->d_basis, h->d_dnode)
     FP2_SWITCH(FP2_LOC)
 #undef FP2_LOC
+    return hipGetLastError();
+}
+
+// Small calls (at most kPoint2Max points, so a pass has at most that many).
+hipError_t launch_point2(const fp2_handle *h, const Loc2 &a, int *code, int *el, double *rs,
+                         double *dist2, hipStream_t s)
+{
+    const int nblk = (a.npts + kPoint2Groups - 1) / kPoint2Groups;
+#define FP2_PT(N1) k2_point<N1><<<nblk, kWave, 0, s>>>(a, h->d_basis, code, el, rs, dist2)
+    FP2_SWITCH(FP2_PT)
+#undef FP2_PT
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    k2_point_stats<<<1, 1024, 0, s>>>(a.pt_part, nblk, h->stats);
+    return hipGetLastError();
+}
+
+hipError_t launch_eval_point2(const fp2_handle *h, const Ev2 &a, hipStream_t s)
+{
+    const int nblk = (a.npts + kPoint2Groups - 1) / kPoint2Groups;
+#define FP2_EVP(N1) k2_eval_point<N1><<<nblk, kWave, 0, s>>>(a, h->d_basis)
+    FP2_SWITCH(FP2_EVP)
+#undef FP2_EVP
     return hipGetLastError();
 }
 
@@ -1093,6 +1146,8 @@ extern "C" int findpts2_setup(fp2_handle **out, const double *x, const double *y
     FP2_HIP(dalloc2(h, &h->ev_pos, M));
     FP2_HIP(dalloc2(h, &h->redo, M));
     FP2_HIP(dalloc2(h, &h->cand_part, (M + 255) / 256));
+    FP2_HIP(dalloc2(h, &h->pt_part, (std::min(M, (size_t)kPoint2Max) + kPoint2Groups - 1) /
+                                        kPoint2Groups * kPoint2Counters));
     FP2_HIP(dalloc2(h, &h->ev_order, M));
     FP2_HIP(hipStreamSynchronize(s));
     *out = h;
@@ -1153,6 +1208,13 @@ extern "C" int findpts2(fp2_handle *h, int npts, const double *pts, const int *p
         a.res_dl = h->res_dl;
         a.iter_part = h->iter_part;
         a.cand_part = h->cand_part;
+        a.pt_part = h->pt_part;
+        if (npts <= kPoint2Max) {
+            a.obb = h->obb;
+            FP_HIP(launch_point2(h, a, code + start, el + start, rs + 2 * (long long)start,
+                                 dist2 + start, s));
+            continue;
+        }
         const int pb = (n + 255) / 256;
         for (int round = 0; round < 2; ++round) {
             a.obb = round == 0 ? h->obb : nullptr;
@@ -1224,6 +1286,10 @@ extern "C" int findpts2_eval(fp2_handle *h, int npts, const int *code, const int
             a.out_all = out + start;
             a.nf_all = nfields;
             for (int f = 0; f < nf; ++f) a.f[f] = h_fields[f0 + f];
+            if (npts <= kPoint2Max) {
+                FP_HIP(launch_eval_point2(h, a, s));
+                continue;
+            }
             if (f0 == 0) {
                 FP_HIP(fill_int(h->elem_cnt, 0, (long long)h->E + 1, s));
                 k2_ev_count<<<pb, 256, 0, s>>>(a);
