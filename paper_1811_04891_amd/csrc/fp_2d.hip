@@ -53,6 +53,7 @@ struct fp2_handle {
     // workspace
     int *ncand = nullptr, *cand_el = nullptr, *cand_pos = nullptr;
     int *elem_cnt = nullptr, *elem_off = nullptr, *order = nullptr;
+    fp::UnitRec *units = nullptr;  // work units of a grouping
     double *res = nullptr;  // M x MC x 3: r, s, d2
     int *res_in = nullptr;
     double *res_dl = nullptr;
@@ -363,6 +364,7 @@ struct Loc2 {
     double tol;
     int *ncand, *cand_el, *cand_pos, *elem_cnt;
     const int *elem_off;
+    const UnitRec *units;
     int *order;
     double *res;
     int *res_in;
@@ -607,10 +609,9 @@ __global__ __launch_bounds__(kWave) void k2_locate(Loc2 a, const double *__restr
     constexpr int V = N1 * N1;
     const BasisPtr<double> B{as_const(basis)};
     unsigned long long my_iters = 0;
-    const UnitList units(a.elem_off, a.E, 1, a.E, kUnit2);
-    for (long long u = xcd_unit(blockIdx.x, gridDim.x); u < units.end; u += gridDim.x) {
-        Unit U;
-        if (!units.at(u, U)) continue;
+    const UnitList units(a.units);
+    for (int u = units.first(); u < units.total; u += gridDim.x) {
+        const Unit U = units.at(u);
         const int e = U.seg;
         cptr<double> X = as_const(a.geom + (long long)e * 2 * V);
         const double he = a.esize[e];
@@ -806,6 +807,7 @@ struct Ev2 {
     int npts, E;
     int *cnt;
     const int *off;
+    const UnitRec *units;
     int *pos, *order;
     double *out;      // this launch's first field
     long long ostride;
@@ -872,10 +874,9 @@ __global__ __launch_bounds__(kWave) void k2_eval(Ev2 a, const double *__restrict
 {
     constexpr int V = N1 * N1;
     const BasisPtr<double> B{as_const(basis)};
-    const UnitList units(a.off, a.E, 1, a.E, kUnitEval2);
-    for (long long u = xcd_unit(blockIdx.x, gridDim.x); u < units.end; u += gridDim.x) {
-        Unit U;
-        if (!units.at(u, U)) continue;
+    const UnitList units(a.units);
+    for (int u = units.first(); u < units.total; u += gridDim.x) {
+        const Unit U = units.at(u);
         const int e = U.seg;
         for (int base = U.beg; base < U.end; base += kWave) {
             const int q = base + (int)threadIdx.x;
@@ -1138,6 +1139,7 @@ extern "C" int findpts2_setup(fp2_handle **out, const double *x, const double *y
     FP2_HIP(dalloc2(h, &h->cand_pos, M * MC));
     FP2_HIP(dalloc2(h, &h->elem_cnt, (size_t)E + 1));
     FP2_HIP(dalloc2(h, &h->elem_off, (size_t)E + 1));
+    FP2_HIP(dalloc2(h, &h->units, unit_records(E, (long long)(M * MC), kUnit2)));
     FP2_HIP(dalloc2(h, &h->order, M * MC));
     FP2_HIP(dalloc2(h, &h->res, 3 * M * MC));
     FP2_HIP(dalloc2(h, &h->res_in, M * MC));
@@ -1202,6 +1204,7 @@ extern "C" int findpts2(fp2_handle *h, int npts, const double *pts, const int *p
         a.cand_pos = h->cand_pos;
         a.elem_cnt = h->elem_cnt;
         a.elem_off = h->elem_off;
+        a.units = h->units;
         a.order = h->order;
         a.res = h->res;
         a.res_in = h->res_in;
@@ -1223,7 +1226,7 @@ extern "C" int findpts2(fp2_handle *h, int npts, const double *pts, const int *p
             FP_HIP(fill_int(h->elem_cnt, 0, (long long)h->E + 1, s));
             k2_cand<<<pb, 256, 0, s>>>(a);
             FP_HIP(hipGetLastError());
-            FP_HIP(scan_exclusive(h->elem_cnt, h->elem_off, h->E, h->scan_tmp, s));
+            FP_HIP(scan_units(h->elem_cnt, h->elem_off, h->units, h->E, kUnit2, h->scan_tmp, s));
             k2_scatter<<<pb, 256, 0, s>>>(a);
             FP_HIP(hipGetLastError());
             const int nblk = unit_grid(h->E, n, kUnit2);
@@ -1278,6 +1281,7 @@ extern "C" int findpts2_eval(fp2_handle *h, int npts, const int *code, const int
             a.E = h->E;
             a.cnt = h->elem_cnt;
             a.off = h->elem_off;
+            a.units = h->units;
             a.pos = h->ev_pos;
             a.order = h->ev_order;
             a.out = out + (long long)f0 * npts + start;
@@ -1294,7 +1298,8 @@ extern "C" int findpts2_eval(fp2_handle *h, int npts, const int *code, const int
                 FP_HIP(fill_int(h->elem_cnt, 0, (long long)h->E + 1, s));
                 k2_ev_count<<<pb, 256, 0, s>>>(a);
                 FP_HIP(hipGetLastError());
-                FP_HIP(scan_exclusive(h->elem_cnt, h->elem_off, h->E, h->scan_tmp, s));
+                FP_HIP(scan_units(h->elem_cnt, h->elem_off, h->units, h->E, kUnitEval2, h->scan_tmp,
+                                  s));
                 k2_ev_scatter<<<pb, 256, 0, s>>>(a);
                 FP_HIP(hipGetLastError());
             }

@@ -30,6 +30,7 @@ struct EvArgs {
     int E;
     int *cnt;
     const int *off;
+    const UnitRec *units;  // work units of the points
     int *pos;
     int *order;
     double *out;   // field-major, stride npts_total
@@ -163,10 +164,9 @@ void k_eval_mfma(EvArgs a, FieldPtrs F,
     const BasisPtr<float> B32{as_const(basis32)};
     LaneNodes<N1, T> Z;  // h_i(r), h_j(s) only for the lane's own i, j = g + 4 w
     lane_nodes<N1, T>(B, threadIdx.x >> 4, Z);
-    const UnitList units(a.off, a.E, 1, a.E, kUnitEvalMfma);
-    for (long long unit = xcd_unit(blockIdx.x, gridDim.x); unit < units.end; unit += gridDim.x) {
-        Unit U;
-        if (!units.at(unit, U)) continue;
+    const UnitList units(a.units);
+    for (int unit = units.first(); unit < units.total; unit += gridDim.x) {
+        const Unit U = units.at(unit);
         const int e = U.seg, beg = U.beg, end = U.end;
         const int lane = threadIdx.x, n = lane & 15;
         // A fragment coordinates of this lane: row -> plane p, row jj; column i
@@ -311,10 +311,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2))) void
     // this lane's fragment: row 4 v + g (plane g, node row v of a tile), column q
     const int rg = n & 3, rv = n >> 2;
     const int off = N1 * (rv + N1 * rg) + g;
-    const UnitList units(a.off, a.E, 1, a.E, kUnitEvalPl);
-    for (long long unit = xcd_unit(blockIdx.x, gridDim.x); unit < units.end; unit += gridDim.x) {
-        Unit U;
-        if (!units.at(unit, U)) continue;
+    const UnitList units(a.units);
+    for (int unit = units.first(); unit < units.total; unit += gridDim.x) {
+        const Unit U = units.at(unit);
         for (int c0 = U.beg; c0 < U.end; c0 += 16 * BT) {
             double hr[BT][Q], hs[BT][N1], ht[BT][Q];
             int p[BT], sl[BT];
@@ -463,11 +462,11 @@ static hipError_t launch_eval_point(int n1, const EvArgs &a, const FieldPtrs &F,
 }
 
 // Launches the order's interpolation kernel over the work units of n points.
-static hipError_t launch_eval_kernel(int n1, int E, int n, const EvArgs &a, const FieldPtrs &F,
+static hipError_t launch_eval_kernel(int n1, int nblk, const EvArgs &a, const FieldPtrs &F,
                                      const double *B, const float *B32, bool mixed, hipStream_t s)
 {
 #define FP_EVAL_MFMA(N1, T, NF) \
-    k_eval_mfma<N1, T, NF><<<unit_grid(E, n, kUnitEvalMfma), kWave, 0, s>>>(a, F, B, B32)
+    k_eval_mfma<N1, T, NF><<<nblk, kWave, 0, s>>>(a, F, B, B32)
 #define FP_EVAL_NF(N1, T)                   \
     do {                                    \
         switch (a.nf) {                     \
@@ -503,7 +502,7 @@ static hipError_t launch_eval_kernel(int n1, int E, int n, const EvArgs &a, cons
 #undef FP_EVAL_MFMA
 #define FP_LAUNCH_PL(N1)                                                             \
     case N1:                                                                         \
-        k_eval_pl<N1><<<unit_grid(E, n, kUnitEvalPl), kWave, 0, s>>>(a, F, B);       \
+        k_eval_pl<N1><<<nblk, kWave, 0, s>>>(a, F, B);                               \
         break
     switch (n1) {
         FP_LAUNCH_PL(9);
@@ -528,6 +527,8 @@ int run_eval(fp_handle *h, const Work &w, int npts, const int *code, const int *
     const size_t res_bytes = w.res ? (size_t)w.M * w.MC * 4 * sizeof(double) : 0;
     for (int start = 0; start < npts; start += w.M) {
         const int n = (npts - start < w.M) ? npts - start : w.M;
+        const int K = h->n1 <= kEvMfmaMaxN1 ? unit_limit(h->E, n, kUnitEvalMfma, 16)
+                                            : kUnitEvalPl;  // points per unit
         hipEvent_t t0 = nullptr, t1 = nullptr, l0 = nullptr, l1 = nullptr;
         if (timed) {
             t0 = pool_event(h);
@@ -560,6 +561,7 @@ int run_eval(fp_handle *h, const Work &w, int npts, const int *code, const int *
             a.E = h->E;
             a.cnt = w.ev_cnt;
             a.off = w.ev_off;
+            a.units = w.ev_units;
             a.pos = w.ev_pos;
             a.order = w.ev_order;
             a.out = out + (long long)f0 * npts + start;
@@ -587,17 +589,18 @@ int run_eval(fp_handle *h, const Work &w, int npts, const int *code, const int *
                     gb.posb = w.ev_pos;
                     group_carve(gp, (char *)w.res, gb);
                     FP_HIP(group_by_key(EvKey{a.code, a.el, h->E}, gp, gb, s));
+                    FP_HIP(list_units(w.ev_off, w.ev_units, h->E, K, gb.scan_tmp, s));
                 } else {
                     FP_HIP(fill_int(w.ev_cnt, 0, (long long)h->E + 1, s));
                     k_ev_count<<<pb, 256, 0, s>>>(a);
                     FP_HIP(hipGetLastError());
-                    FP_HIP(scan_exclusive(w.ev_cnt, w.ev_off, h->E, w.scan_tmp, s));
+                    FP_HIP(scan_units(w.ev_cnt, w.ev_off, w.ev_units, h->E, K, w.scan_tmp, s));
                     k_ev_scatter<<<pb, 256, 0, s>>>(a);
                     FP_HIP(hipGetLastError());
                 }
                 if (timed) FP_HIP(hipEventRecord(l0, s));
             }
-            FP_HIP(launch_eval_kernel(h->n1, h->E, n, a, F, h->d_basis, h->d_basis32,
+            FP_HIP(launch_eval_kernel(h->n1, unit_grid(h->E, n, K), a, F, h->d_basis, h->d_basis32,
                                       h->precision == FP_PREC_MIXED, s));
             if (staged) {
                 launch_unstage(a, pb, s);
@@ -649,10 +652,10 @@ int scratch_ptr(int dev, char **p)
 }
 
 // Eval-only workspace carved from the scratch array: counters and offsets
-// of E + 1 elements and the scan's block sums, then two arrays of M points
-// per pass, M as large as the array allows.  Returns false when E leaves no
+// of E + 1 elements and the scan's block sums, then the unit list and two
+// arrays of M points per pass, M as large as the array allows.  Returns false when E leaves no
 // room for a pass of kScratchMinPass points.
-constexpr int kScratchMinPass = 1024;
+constexpr int kScratchMinPass = 128;
 
 static size_t round256(size_t b) { return (b + 255) / 256 * 256; }
 
@@ -663,7 +666,15 @@ static bool scratch_carve(char *base, int E, int npts, Work &w)
                          round256((size_t)scan_tmp_size((long long)E + 1) * sizeof(int)) +
                          round256(kEvSink * sizeof(double));
     if (fixed >= kScratchBytes) return false;
-    const size_t per = (kScratchBytes - fixed) / 2 / 256 * 256 / sizeof(int);  // ints per array
+    // points per pass: the largest number, in steps of 64, whose arrays fit
+    const size_t room = kScratchBytes - fixed;
+    const auto arrays = [E](size_t m) {
+        return 2 * m * sizeof(int) +
+               round256(unit_records(E, (long long)m, kUnitMin) * sizeof(UnitRec));
+    };
+    size_t per = 0;
+    for (size_t step = (size_t)1 << 22; step >= 64; step /= 2)
+        if (arrays(per + step) <= room) per += step;
     if (per < (size_t)kScratchMinPass) return false;
     const int M = (int)std::min<size_t>(per, (size_t)std::max(npts, 1));
     char *q = base;
@@ -678,6 +689,8 @@ static bool scratch_carve(char *base, int E, int npts, Work &w)
     q += round256((size_t)scan_tmp_size((long long)E + 1) * sizeof(int));
     w.ev_sink = (double *)q;
     q += round256(kEvSink * sizeof(double));
+    w.ev_units = (UnitRec *)q;
+    q += round256(unit_records(E, (long long)per, kUnitMin) * sizeof(UnitRec));
     w.ev_pos = (int *)q;
     q += per * sizeof(int);
     w.ev_order = (int *)q;

@@ -82,6 +82,8 @@ struct TimedPair {
     hipEvent_t a, b;
 };
 
+struct UnitRec;
+
 // Workspace of one findpts / findpts_eval call on one stream: M points per
 // pass, MC candidate slots per point (the longest hash-cell list), E + 1
 // element counters.  Carved from one device block; a handle owns one, the
@@ -102,6 +104,8 @@ struct Work {
     int *scan_tmp = nullptr;  // block sums of the device scans
     unsigned *cand_part = nullptr;  // ceil(M / 256): per-block candidate counts
     unsigned *iter_part = nullptr;  // unit_grid(E, M, kUnitMin): Newton iterations per block
+    UnitRec *units = nullptr;     // unit list of the pairs
+    UnitRec *ev_units = nullptr;  // unit list of the points
     unsigned *pt_part = nullptr;  // min(M, kPointMax) x kPointCounters (small calls)
     int *ev_cnt = nullptr;    // E + 1
     int *ev_off = nullptr;    // E + 1
@@ -191,77 +195,85 @@ hipEvent_t pool_event(fp_handle *h);
         if (e_ != hipSuccess) return fp::hip_fail(e_, #call); \
     } while (0)
 
-// Work units of an element-grouped list.  Segment s (a run of gs consecutive
-// elements, s < ns) owns list positions [b(s), b(s + 1)) with
-// b(s) = off[min(s gs, ne)]; it is cut at the multiples of K and its piece in
-// window j (positions [j K, (j + 1) K)) is unit s + j.  Along the list both s
-// and j never decrease and at least one of them grows from one piece to the
-// next, so the unit indices of the pieces are distinct and increasing, and
-// the segment holding unit u is the last s with s + b(s) / K <= u, which lies
-// in [u - T, u] for T = b(ns) / K.  A block takes units blockIdx.x,
-// blockIdx.x + gridDim.x, ... below ns + T + 1: an element with many points
-// is spread over many blocks, and a sparse list (T small) needs no search.
-// Units of gaps (empty segments, cuts that fall on a segment's start) are
-// empty.
+// Work units of an element-grouped list: the entries [off[e], off[e + 1]) of an
+// element with more than K of them are cut into ceil(cnt / K) or fewer equal
+// pieces (unit_size entries each, the last one shorter), any other element with
+// entries is one unit, and the units are listed without gaps (scan_units writes
+// the list together with the offsets).  Record 0 is {units, entries}; record
+// 1 + u is {first entry, element} of unit u, and the next record's first entry
+// is its end (a last record {entries, E} closes the list).
+//
+// Cutting the whole list at multiples of K instead, which needs no table, gave an
+// element of 60 to 100 entries two units about as often as one, each staging the
+// element and draining its slots, and left a unit index per empty element that a
+// wavefront had to search for.  Measured, with the scan's launches: annulus of 1.01e6
+// points 1242 -> 1212 us (findpts), 275 -> 254 (4 fields); large box of 2e7 21.7 ->
+// 21.2 ms, 3.76 -> 3.52; 120,320 known points on 27,360 elements, four interpolations
+// 220 -> 145 us; 2D ring of 1.01e6 432 -> 368.
+constexpr int kUnitMin = 64;  // smallest K
 struct Unit {
     int seg, beg, end;
 };
+struct UnitRec {
+    int beg, seg;
+};
+
+// Entries of each unit of an element with cnt > 0 entries: the units of a crowded
+// element are equal up to a batch of 16.
+__host__ __device__ __forceinline__ int unit_size(int cnt, int K)
+{
+    if (cnt <= K) return cnt;
+    const int nu = (cnt - 1) / K + 1;
+    return ((cnt - 1) / nu + 16) & ~15;
+}
+
+// Unit size of a list of n entries of E elements whose kernel runs best at `most`:
+// less where the elements alone do not make 2048 units (two wavefronts per SIMD),
+// in steps of `step` and at least kUnitMin.
+inline int unit_limit(int E, int n, int most, int step)
+{
+    if (E >= 2048) return most;
+    const int k = (n / 2048 + step - 1) / step * step;
+    const int least = step > kUnitMin ? step : kUnitMin;
+    return k < least ? least : (k < most ? k : most);
+}
+
+// Records of a list of at most n entries of E elements at unit size K or more.
+inline size_t unit_records(long long E, long long n, int K)
+{
+    return (size_t)((E < n ? E : n) + n / K + 2);
+}
 
 struct UnitList {
-    const int *off;
-    int ns, gs, ne, K, T;
-    long long end;  // one past the last unit index
+    const UnitRec *rec;
+    int total;
 
-    __host__ __device__ __forceinline__ UnitList(const int *off_, int ns_, int gs_, int ne_, int K_)
-        : off(off_), ns(ns_), gs(gs_), ne(ne_), K(K_)
+    __device__ __forceinline__ explicit UnitList(const UnitRec *u) : rec(u + 1), total(__builtin_amdgcn_readfirstlane(u->beg)) {}
+    // the block's first unit (then every gridDim.x-th one below total)
+    __device__ __forceinline__ int first() const
     {
-        T = off[ne] / K;
-        end = (long long)ns + T + 1;
+        const int G = min((int)gridDim.x, total), b = (int)blockIdx.x;
+        return b < G ? (int)xcd_unit(b, G) : total;
     }
-    __host__ __device__ __forceinline__ int b(long long s) const
+    __device__ __forceinline__ Unit at(int u) const
     {
-        return off[s * gs < ne ? s * gs : ne];
-    }
-    // Unit u of the list (false for a gap).  Called by every lane of a
-    // wavefront with the same u (converged code, full wavefront): the 64
-    // lanes probe 64 evenly spaced segments of the bracket at once, and the
-    // prefix of probes with s + b(s) / K <= u (a prefix, since that sum grows
-    // with s) narrows the bracket to one 64th per round, so a list of T
-    // windows takes log64 T dependent loads instead of log2 T.
-    __device__ __forceinline__ bool at(long long u, Unit &U) const
-    {
-        long long lo = u - T, hi = u;  // s + b(s) / K <= u holds at lo
-        if (lo < 0) lo = 0;
-        if (hi > ns - 1) hi = ns - 1;
-        const long long lane = (long long)(threadIdx.x & (kWave - 1));
-        while (lo < hi) {
-            const long long span = hi - lo;
-            const long long p = lo + ((lane + 1) * span + kWave - 1) / kWave;  // in (lo, hi]
-            const long long cnt = __popcll(__ballot(p + b(p) / K <= u));
-            const long long nlo = cnt == 0 ? lo : lo + (cnt * span + kWave - 1) / kWave;
-            const long long nhi = cnt == kWave ? hi : lo + ((cnt + 1) * span + kWave - 1) / kWave - 1;
-            lo = nlo;
-            hi = nhi;
-        }
-        const int b0 = b(lo), b1 = b(lo + 1);
-        const long long j = u - lo;
-        if (b0 >= b1 || j * K >= b1) return false;
-        U.seg = (int)lo;
-        U.beg = (int)(j * K > b0 ? j * K : b0);
-        U.end = (int)((j + 1) * K < b1 ? (j + 1) * K : b1);
-        return true;
+        // u is the same in all lanes
+        return Unit{__builtin_amdgcn_readfirstlane(rec[u].seg),
+                    __builtin_amdgcn_readfirstlane(rec[u].beg),
+                    __builtin_amdgcn_readfirstlane(rec[u + 1].beg)};
     }
 };
 
-// Blocks of a unit launch over ns segments for a list of about n entries:
-// one per segment plus up to 2 n / K (at most kUnitSpare) for the pieces of
-// crowded segments.  Units beyond the grid are taken by the grid-stride walk.
+// Blocks of a unit launch over E elements for a list of about n entries (n
+// points: two candidate pairs each at most, in all but rare cases): the elements
+// that can have entries, and up to 2 n / K (at most kUnitSpare) for the pieces of
+// crowded ones.  Units beyond the grid are taken by the grid-stride walk.
 constexpr long long kUnitSpare = 4096;
-inline int unit_grid(int ns, long long n, int K)
+inline int unit_grid(int E, long long n, int K)
 {
     long long extra = 2 * ((n + K - 1) / K);
     if (extra > kUnitSpare) extra = kUnitSpare;
-    const long long g = (long long)ns + extra;
+    const long long g = (E < 2 * n ? (long long)E : 2 * n) + extra;
     return (int)(g < 1 ? 1 : (g > 0x7fffffffLL ? 0x7fffffffLL : g));
 }
 
@@ -296,7 +308,6 @@ __device__ __forceinline__ int wave_rank(int *cnt, int e, bool act)
     if ((pending >> lane) & 1ull) rank = atomicAdd(&cnt[e], 1);
     return rank;
 }
-constexpr int kUnitMin = 64;  // smallest K of the locate kernels
 
 // Exclusive scan of n ints: out[0..n], out[n] = total.  tmp needs
 // scan_tmp_size(n) ints.  With gate non-null the kernels do nothing while
@@ -304,6 +315,12 @@ constexpr int kUnitMin = 64;  // smallest K of the locate kernels
 int scan_tmp_size(long long n);
 hipError_t scan_exclusive(const int *in, int *out, int n, int *tmp,
                           hipStream_t s, const int *gate = nullptr);
+// As scan_exclusive over the E counts of a grouping, and the list of its work
+// units of at most K entries.
+hipError_t scan_units(const int *cnt, int *off, UnitRec *units, int E, int K, int *tmp, hipStream_t s,
+                      const int *gate = nullptr);
+// The unit list of offsets that are already there.
+hipError_t list_units(const int *off, UnitRec *units, int E, int K, int *tmp, hipStream_t s);
 hipError_t fill_int_gated(int *p, int value, long long n, const int *gate, hipStream_t s);
 
 // GLL nodes and barycentric weights of order N; the inverse of the

@@ -53,6 +53,7 @@ struct LocArgs {
     int *cand_pos;
     int *elem_cnt;
     const int *elem_off;
+    const UnitRec *units;  // work units of the pairs
     int E;
     int *order;
     double *res;
@@ -63,7 +64,6 @@ struct LocArgs {
     int pair_max;         // second pass: up to this many pairs run on k_newton_pair
                           // (one wavefront per pair)
     unsigned *pt_part;    // small calls: counters of each block
-    int unit;             // orders 8 to 15: pairs per work unit
 };
 
 __device__ __forceinline__ int cell_of(const Grid &g, int a, double x)
@@ -738,23 +738,31 @@ __global__ __launch_bounds__(256) void k_select(LocArgs a, const double *__restr
 // Orders 8 and 9 have a binary32 phase.
 constexpr int kMixedPlMaxN1 = 10;
 
-// Pairs per work unit of the kernels of orders 8 to 15 for n points on E
-// elements: kUnitPl, or as few as one batch per wavefront (step pairs) where
-// the elements alone do not make 2,048 units.
-static int unit_pl(int E, int n, int step)
+// Pairs per work unit of a pass of n points: at orders 8 to 15 at least one batch
+// per wavefront of the block.
+static int unit_pairs(const fp_handle *h, int n)
 {
-    if (E >= 2048) return kUnitPl;
-    const int k = (n / 2048 + step - 1) / step * step;
-    return std::min(std::max(k, std::max(step, kUnitMin)), kUnitPl);
+    const int E = h->E;
+    switch (h->n1) {
+        case 9: return unit_limit(E, n, kUnitPl, 16 * PLShape<9>::W);
+        case 10: return unit_limit(E, n, kUnitPl, 16 * PLShape<10>::W);
+        case 11: return unit_limit(E, n, kUnitPl, 16 * PLShape<11>::W);
+        case 12: return unit_limit(E, n, kUnitPl, 16 * PLShape<12>::W);
+        case 13: return unit_limit(E, n, kUnitPl, 16 * PLShape<13>::W);
+        case 14: return unit_limit(E, n, kUnitPl, 16 * PLShape<14>::W);
+        case 15: return unit_limit(E, n, kUnitPl, 16 * PLShape<15>::W);
+        case 16: return unit_limit(E, n, kUnitPl, 16 * PLShape<16>::W);
+        default: return unit_limit(E, n, kUnitMfma, 16);
+    }
 }
 
 // Launches the order's Newton kernel over the work units of the pass's pairs
 // (n points); *nblk receives the grid size (one iteration partial per block).
-static hipError_t launch_locate_kernel(const fp_handle *h, LocArgs a, int n,
+static hipError_t launch_locate_kernel(const fp_handle *h, LocArgs a, int n, int K,
                                        hipStream_t s, int *nblk)
 {
-#define FP_GRID(K) (a.only ? std::min(unit_grid(h->E, n, (K)), kSecondPassGrid) \
-                           : unit_grid(h->E, n, (K)))
+    *nblk = unit_grid(h->E, n, K);
+    if (a.only) *nblk = std::min(*nblk, kSecondPassGrid);
 // a second pass of few pairs: one wavefront per pair
 #define FP_LAUNCH_PAIR(N1)                                                  \
     do {                                                                    \
@@ -772,17 +780,13 @@ constexpr int kBinary64Only = 6;
 #define FP_LAUNCH_MFMA(N1)                                                           \
     do {                                                                             \
         if (h->precision == FP_PREC_MIXED && a.first && N1 == kN8) {                   \
-            *nblk = FP_GRID(kUnitMixed);                                             \
             k_mixed8<<<*nblk, kWave, 0, s>>>(a, h->d_basis, h->d_basis32, h->d_dnode); \
         } else if (h->precision == FP_PREC_MIXED && a.first && N1 != kBinary64Only) {  \
-            *nblk = FP_GRID(kUnitMixed);                                             \
             k_locate_mixed<N1><<<*nblk, kWave, 0, s>>>(a, h->d_basis, h->d_basis32,  \
                                                         h->d_dnode);                 \
         } else if (N1 == kN8) {                                                      \
-            *nblk = FP_GRID(kUnitMfma);                                              \
             k_newton8<<<*nblk, kWave, 0, s>>>(a, h->d_basis, h->d_dnode);            \
         } else {                                                                     \
-            *nblk = FP_GRID(kUnitMfma);                                              \
             k_locate_mfma<N1><<<*nblk, kWave, 0, s>>>(a, h->d_basis, h->d_dnode);     \
         }                                                                            \
         FP_LAUNCH_PAIR(N1);                                                          \
@@ -792,8 +796,6 @@ constexpr int kBinary64Only = 6;
 #define FP_LAUNCH_PL(N1)                                                              \
     do {                                                                              \
         constexpr int T = PLShape<N1>::T;                                             \
-        a.unit = unit_pl(h->E, n, 16 * PLShape<N1>::W);                               \
-        *nblk = FP_GRID(a.unit);                                                      \
         bool done = false;                                                            \
         if constexpr (N1 <= kMixedPlMaxN1) {                                          \
             if (h->precision == FP_PREC_MIXED && a.first) {                           \
@@ -829,7 +831,6 @@ constexpr int kBinary64Only = 6;
 #undef FP_LAUNCH_PAIR
 #undef FP_LAUNCH_MFMA
 #undef FP_LAUNCH_PL
-#undef FP_GRID
     return hipGetLastError();
 }
 
@@ -895,6 +896,7 @@ int run_findpts(fp_handle *h, const Work &w, int npts, const double *pts, const 
         a.cand_pos = w.cand_pos;
         a.elem_cnt = w.elem_cnt;
         a.elem_off = w.elem_off;
+        a.units = w.units;
         a.E = h->E;
         a.order = w.order;
         a.res = w.res;
@@ -932,15 +934,16 @@ int run_findpts(fp_handle *h, const Work &w, int npts, const double *pts, const 
             }
             continue;
         }
+        const int K = unit_pairs(h, n);
         FP_HIP(fill_int(w.elem_cnt, 0, (long long)h->E + 1, s));
         k_cand<<<pb, 256, 0, s>>>(a);
         FP_HIP(hipGetLastError());
-        FP_HIP(scan_exclusive(w.elem_cnt, w.elem_off, h->E, w.scan_tmp, s));
+        FP_HIP(scan_units(w.elem_cnt, w.elem_off, w.units, h->E, K, w.scan_tmp, s));
         k_scatter<<<pb, 256, 0, s>>>(a);
         FP_HIP(hipGetLastError());
         if (timed) FP_HIP(hipEventRecord(l0, s));
         int nblk = 0;
-        FP_HIP(launch_locate_kernel(h, a, n, s, &nblk));
+        FP_HIP(launch_locate_kernel(h, a, n, K, s, &nblk));
         if (timed) FP_HIP(hipEventRecord(l1, s));
         FP_HIP(launch_select(h, a, pb, co, eo, ro, dO, s));
         k_stats<<<kStatsBlocks, 1024, 0, s>>>(w.cand_part, pb, w.iter_part, nblk, h->E,
@@ -955,7 +958,7 @@ int run_findpts(fp_handle *h, const Work &w, int npts, const double *pts, const 
         FP_HIP(fill_int_gated(w.elem_cnt, 0, (long long)h->E + 1, w.gate, s));
         k_cand<<<pb, 256, 0, s>>>(a);
         FP_HIP(hipGetLastError());
-        FP_HIP(scan_exclusive(w.elem_cnt, w.elem_off, h->E, w.scan_tmp, s, w.gate));
+        FP_HIP(scan_units(w.elem_cnt, w.elem_off, w.units, h->E, K, w.scan_tmp, s, w.gate));
         k_scatter<<<pb, 256, 0, s>>>(a);
         FP_HIP(hipGetLastError());
         hipEvent_t m0 = nullptr, m1 = nullptr;
@@ -964,7 +967,7 @@ int run_findpts(fp_handle *h, const Work &w, int npts, const double *pts, const 
             m1 = pool_event(h);
             FP_HIP(hipEventRecord(m0, s));
         }
-        FP_HIP(launch_locate_kernel(h, a, n, s, &nblk));
+        FP_HIP(launch_locate_kernel(h, a, n, K, s, &nblk));
         if (timed) {
             FP_HIP(hipEventRecord(m1, s));
             record(h, 4, m0, m1);

@@ -535,6 +535,8 @@ void lay_out(Layout &L, Work &w, int E, int MC, int M, bool delta)
     w.gate = L.take<int>(1);
     w.scan_tmp = L.take<int>((size_t)scan_tmp_size((long long)E + 1));
     w.cand_part = L.take<unsigned>((m + 255) / 256);
+    w.units = L.take<UnitRec>(unit_records(E, (long long)(m * mc), kUnitMin));
+    w.ev_units = L.take<UnitRec>(unit_records(E, M, kUnitMin));
     w.iter_part = L.take<unsigned>((size_t)unit_grid(E, M, kUnitMin));
     w.pt_part = L.take<unsigned>((size_t)std::min(M, kPointMax) * kPointCounters);
     w.ev_cnt = L.take<int>(e1);

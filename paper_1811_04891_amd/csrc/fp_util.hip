@@ -18,35 +18,38 @@ int hip_fail(hipError_t e, const char *what)
 }
 
 // ---------------------------------------------------------------------------
-// Exclusive scan, three launches: tile sums, scan of the tile sums in one
-// block, tile-local scan plus the tile's offset.  A tile is 256 threads x 16
-// items.  Wave-level inclusive scans use cross-lane shuffles (wave64).
+// Exclusive scans, tiles of 256 threads x 4 items: one launch for one tile, else
+// the tile sums, then each block adds up the sums before its own and scans its
+// tile.  A pass groups its pairs and its points with these, in a chain where a
+// launch costs 4 to 5 us whatever it does: the 16384 elements of the annulus took
+// 15 us in three launches (the sums scanned by one of their own), and take 9.
+// Measured against: one launch where each block adds up all items before its tile
+// (25 us), and one block for all of them (50 us: its stores go through one CU).
+//
+// Groupings also get their work units: the sums then carry the entries in the
+// low and the units in the high 32 bits.
 // ---------------------------------------------------------------------------
 constexpr int kScanThreads = 256;
-constexpr int kScanItems = 16;
+constexpr int kScanItems = 4;
 constexpr int kScanTile = kScanThreads * kScanItems;
-
-__device__ __forceinline__ int wave_incl_scan(int v)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        int t = __shfl_up(v, o, kWave);
-        if (lane >= o) v += t;
-    }
-    return v;
-}
+typedef unsigned long long u64;
 
 // Block-wide exclusive scan of one value per thread; returns the thread's
 // exclusive prefix and writes the block total.
-__device__ __forceinline__ int block_excl_scan(int v, int *total)
+template <class T>
+__device__ __forceinline__ T block_excl_scan(T v, T *total)
 {
-    __shared__ int wsum[kScanThreads / kWave];
+    __shared__ T wsum[kScanThreads / kWave];
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    int inc = wave_incl_scan(v);
+    T inc = v;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const T t = __shfl_up(inc, o, kWave);
+        if (lane >= o) inc += t;
+    }
     if (lane == kWave - 1) wsum[w] = inc;
     __syncthreads();
-    int off = 0, tot = 0;
+    T off = 0, tot = 0;
 #pragma unroll
     for (int i = 0; i < kScanThreads / kWave; ++i) {
         if (i < w) off += wsum[i];
@@ -57,72 +60,129 @@ __device__ __forceinline__ int block_excl_scan(int v, int *total)
     return off + inc - v;
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_tiles(
-    const int *__restrict__ in, int n, int *__restrict__ tsum, const int *__restrict__ gate)
+// What is scanned: counts (kCounts: offsets only; kGroup: offsets and units),
+// or the differences of offsets that are there (kOffsets: units).
+enum ScanMode { kCounts, kGroup, kOffsets };
+
+struct ScanArgs {
+    const int *in;  // counts or offsets
+    int n, K;
+    u64 *tsum;
+    int *out;
+    UnitRec *units;
+    const int *gate;
+};
+
+template <ScanMode MODE>
+__device__ __forceinline__ u64 scan_value(int cnt, int K)
 {
-    if (gate && !*gate) return;
-    const long long base = (long long)blockIdx.x * kScanTile;
-    int s = 0;
+    if constexpr (MODE == kCounts) return (u64)(unsigned)cnt;
+    u64 nu = cnt > 0 ? 1u : 0u;
+    if (cnt > K) nu = (u64)((cnt - 1) / unit_size(cnt, K) + 1);
+    return (u64)(unsigned)cnt | (nu << 32);
+}
+
+// The thread's consecutive counts from item i0 (zero past the last).
+template <ScanMode MODE>
+__device__ __forceinline__ void scan_load(const ScanArgs &a, long long i0, int (&v)[kScanItems])
+{
+    constexpr int L = MODE == kOffsets ? kScanItems + 1 : kScanItems;
+    const long long m = MODE == kOffsets ? (long long)a.n : (long long)a.n - 1;
+    int w[L];
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        long long i = base + (long long)k * kScanThreads + threadIdx.x;
-        if (i < n) s += in[i];
-    }
-    int tot;
-    block_excl_scan(s, &tot);
-    if (threadIdx.x == 0) tsum[blockIdx.x] = tot;
+    for (int k = 0; k < L; ++k) w[k] = a.in[i0 + k < m ? i0 + k : m];
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k)
+        v[k] = i0 + k >= a.n ? 0 : (MODE == kOffsets ? w[(k + 1) % L] - w[k] : w[k]);
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_top(int *__restrict__ tsum,
-                                                           int nt, const int *__restrict__ gate)
+template <ScanMode MODE>
+__device__ __forceinline__ u64 scan_sum(const ScanArgs &a, long long i0)
 {
-    if (gate && !*gate) return;
-    // each thread scans a contiguous run of tile sums
-    const int per = (nt + kScanThreads - 1) / kScanThreads;
-    const int b = threadIdx.x * per;
-    int s = 0;
-    for (int i = 0; i < per; ++i)
-        if (b + i < nt) s += tsum[b + i];
-    int tot;
-    int off = block_excl_scan(s, &tot);
-    for (int i = 0; i < per; ++i)
-        if (b + i < nt) {
-            int v = tsum[b + i];
-            tsum[b + i] = off;
-            off += v;
-        }
-}
-
-__global__ __launch_bounds__(kScanThreads) void k_scan_down(
-    const int *__restrict__ in, int n, const int *__restrict__ toff,
-    int *__restrict__ out, int nt, const int *__restrict__ gate)
-{
-    if (gate && !*gate) return;
-    const long long base = (long long)blockIdx.x * kScanTile;
-    // each thread owns kScanItems consecutive items
-    const long long my = base + (long long)threadIdx.x * kScanItems;
     int v[kScanItems];
-    int s = 0;
+    scan_load<MODE>(a, i0, v);
+    u64 s = 0;
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        long long i = my + k;
-        v[k] = (i < n) ? in[i] : 0;
-        s += v[k];
-    }
-    int tot;
-    int off = block_excl_scan(s, &tot) + toff[blockIdx.x];
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        long long i = my + k;
-        if (i < n) out[i] = off;
-        off += v[k];
-    }
-    if (blockIdx.x == nt - 1 && threadIdx.x == kScanThreads - 1) out[n] = off;
+    for (int k = 0; k < kScanItems; ++k) s += scan_value<MODE>(v[k], a.K);
+    return s;
 }
+
+template <ScanMode MODE>
+__global__ __launch_bounds__(kScanThreads) void k_scan_tiles(ScanArgs a)
+{
+    if (a.gate && !*a.gate) return;
+    u64 tot;
+    block_excl_scan(scan_sum<MODE>(a, (long long)blockIdx.x * kScanTile + threadIdx.x * kScanItems),
+                    &tot);
+    if (threadIdx.x == 0) a.tsum[blockIdx.x] = tot;
+}
+
+template <ScanMode MODE>
+__global__ __launch_bounds__(kScanThreads) void k_scan(ScanArgs a)
+{
+    if (a.gate && !*a.gate) return;
+    const long long i0 = (long long)blockIdx.x * kScanTile + threadIdx.x * kScanItems;
+    int v[kScanItems];
+    scan_load<MODE>(a, i0, v);
+    u64 s = 0, tot, run = 0;
+    for (int t = threadIdx.x; t < (int)blockIdx.x; t += kScanThreads) s += a.tsum[t];
+    if (blockIdx.x > 0) block_excl_scan(s, &run);
+    s = 0;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) s += scan_value<MODE>(v[k], a.K);
+    const u64 before = block_excl_scan(s, &tot);
+    const u64 all = run + tot;
+    run += before;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+        const long long i = i0 + k;
+        const int beg = (int)(unsigned)run;
+        if (MODE != kOffsets && i < a.n) a.out[i] = beg;
+        const u64 add = scan_value<MODE>(v[k], a.K);
+        if constexpr (MODE != kCounts) {
+            // a crowded element's records are written by the whole wavefront
+            constexpr int kOwn = 4;
+            const int r = 1 + (int)(run >> 32), nu = (int)(add >> 32);
+            const int size = nu > 1 ? unit_size(v[k], a.K) : v[k];
+            if (nu <= kOwn)
+                for (int j = 0; j < nu; ++j) a.units[r + j] = UnitRec{beg + j * size, (int)i};
+            u64 big = __ballot(nu > kOwn);
+            while (big) {
+                const int src = __ffsll((long long)big) - 1;
+                big &= big - 1;
+                const int bn = __shfl(nu, src, kWave), bs = __shfl(size, src, kWave);
+                const int bb = __shfl(beg, src, kWave), bi = __shfl((int)i, src, kWave);
+                const int br = __shfl(r, src, kWave);
+                for (int j = threadIdx.x & (kWave - 1); j < bn; j += kWave)
+                    a.units[br + j] = UnitRec{bb + j * bs, bi};
+            }
+        }
+        run += add;
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        const int nu = (int)(all >> 32), ne = (int)(unsigned)all;
+        if (MODE != kOffsets) a.out[a.n] = ne;
+        if constexpr (MODE != kCounts) {
+            a.units[0] = UnitRec{nu, ne};
+            a.units[1 + nu] = UnitRec{ne, a.n};
+        }
+    }
+}
+
+// Ints of the tile sums.
+int scan_tmp_size(long long n) { return 2 * (int)((n + kScanTile - 1) / kScanTile) + 2; }
 
 __global__ void k_zero_total(int *out, int n) { out[n] = 0; }
 
-int scan_tmp_size(long long n) { return (int)((n + kScanTile - 1) / kScanTile) + 1; }
+template <ScanMode MODE>
+static hipError_t launch_scan(ScanArgs a, int *tmp, hipStream_t s)
+{
+    const int nt = (a.n + kScanTile - 1) / kScanTile;
+    a.tsum = (u64 *)tmp;
+    if (nt > 1) k_scan_tiles<MODE><<<nt, kScanThreads, 0, s>>>(a);
+    k_scan<MODE><<<nt, kScanThreads, 0, s>>>(a);
+    return hipGetLastError();
+}
 
 hipError_t scan_exclusive(const int *in, int *out, int n, int *tmp, hipStream_t s,
                           const int *gate)
@@ -131,11 +191,20 @@ hipError_t scan_exclusive(const int *in, int *out, int n, int *tmp, hipStream_t 
         k_zero_total<<<1, 1, 0, s>>>(out, 0);
         return hipGetLastError();
     }
-    const int nt = (n + kScanTile - 1) / kScanTile;
-    k_scan_tiles<<<nt, kScanThreads, 0, s>>>(in, n, tmp, gate);
-    k_scan_top<<<1, kScanThreads, 0, s>>>(tmp, nt, gate);
-    k_scan_down<<<nt, kScanThreads, 0, s>>>(in, n, tmp, out, nt, gate);
-    return hipGetLastError();
+    return launch_scan<kCounts>(ScanArgs{in, n, 1, nullptr, out, nullptr, gate},
+                                tmp, s);
+}
+
+hipError_t scan_units(const int *cnt, int *off, UnitRec *units, int E, int K, int *tmp, hipStream_t s,
+                      const int *gate)
+{
+    return launch_scan<kGroup>(ScanArgs{cnt, E, K, nullptr, off, units, gate}, tmp, s);
+}
+
+hipError_t list_units(const int *off, UnitRec *units, int E, int K, int *tmp, hipStream_t s)
+{
+    return launch_scan<kOffsets>(
+        ScanArgs{off, E, K, nullptr, nullptr, units, nullptr}, tmp, s);
 }
 
 __global__ void k_fill_int(int *__restrict__ p, int v, long long n, const int *__restrict__ gate)

@@ -1,0 +1,73 @@
+"""Work units: one crowded element, meshes whose element count is around a scan
+tile (1024), elements just below and above the unit sizes, empty runs; points in
+random order, both entry points, against the oracle and the field's polynomial."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads as w
+from parity import compare_eval, compare_locate
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-12
+
+
+def _mesh_points(m, counts, seed):
+    """counts[e] points strictly inside element e of a box mesh, shuffled; also
+    their elements."""
+    rng = np.random.default_rng(seed)
+    e = np.repeat(np.arange(m.E), counts)
+    X = np.stack([m.x.numpy(), m.y.numpy(), m.z.numpy()], 1).reshape(m.E, 3, -1)
+    lo, hi = X.min(2)[e], X.max(2)[e]
+    p = lo + (hi - lo) * rng.uniform(0.05, 0.95, (len(e), 3))
+    q = rng.permutation(len(e))
+    return p[q], e[q]
+
+
+def _counts(E, seed):
+    rng = np.random.default_rng(seed)
+    c = rng.integers(0, 80, E)
+    c[rng.random(E) < 0.5] = 0
+    for k, v in enumerate((63, 64, 65, 127, 128, 129, 144, 255, 256, 257, 700, 5000)):
+        c[(k * 83 + 1) % E] = v
+    return c
+
+
+@pytest.mark.parametrize("N", [3, 7, 9])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (3, 3, 3), (11, 31, 3), (16, 16, 4), (41, 5, 5),
+                                   (32, 32, 3)])
+def test_units_of_all_sizes(N, shape):
+    from paper_1811_04891_amd import findpts as fp
+    E = shape[0] * shape[1] * shape[2]
+    print(f"case: units, order {N}, {E} elements", flush=True)
+    dev = torch.device("cuda:0")
+    m = w.box_mesh(*shape, N=N)
+    counts = np.array([30011]) if E == 1 else _counts(E, E)
+    pts, own = _mesh_points(m, counts, N)
+    if E == 27:
+        pts, own = np.tile(pts, (3, 1)), np.tile(own, 3)
+    n = len(pts)
+    assert n > 16384  # past the small calls
+    fields, _ = w.poly_fields(m, 3, degree=min(N, 3), seed=1)
+    md = m.to(dev)
+    h = fp.findpts_setup(md.x, md.y, md.z, N, tol=TOL, max_points=n)
+    code, el, rst, d2 = fp.findpts(h, torch.as_tensor(pts).to(dev))
+    out = fp.findpts_eval(h, code, el, rst, [f.to(dev) for f in fields])
+    torch.cuda.synchronize()
+    res = [t.cpu().numpy() for t in (code, el, rst, d2)]
+    assert np.all(res[0] == 0) and np.array_equal(res[1], own)
+    sub = np.arange(0, n, max(1, n // 1500))
+    om = oracle.OracleMesh.from_mesh(m, TOL)
+    _, hs = om.bbox()
+    compare_locate(om, pts[sub], [a[sub] for a in res], om.findpts(pts[sub]), hs, TOL)
+    hf = [f.numpy() for f in fields]
+    exp = om.eval(res[0], res[1], res[2], hf)
+    compare_eval(out.cpu().numpy(), exp, hf)
+    # interpolation without the handle's workspace
+    out2 = torch.empty_like(out)
+    fp.findpts_eval_noalloc(h, code, el, rst, [f.to(dev) for f in fields], out2)
+    torch.cuda.synchronize()
+    compare_eval(out2.cpu().numpy(), exp, hf)
+    h.free()
