@@ -371,7 +371,35 @@ struct Loc2 {
     double *res_dl;
     unsigned *iter_part;
     unsigned *pt_part;  // small calls: counters of each block
+    bool few;           // rank_few ranks the pairs
 };
+
+// Entries q0 .. q0 + cnt - 1 (at most 64) of the cell lists whose box holds
+// (x, y), four loaded at a time: taken one by one, a wavefront waited on its
+// lists entry by entry (k2_cand on 1.01e6 points of the ring 131 us, 66 now).
+__device__ __forceinline__ unsigned long long cell_hits2(const Loc2 &a, int q0, int cnt, double x,
+                                                         double y)
+{
+    unsigned long long m = 0ull;
+    for (int i = 0; i < cnt; i += 4) {
+        int e[4];
+        double2 bx[4], by[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) e[w] = a.cell_el[q0 + min(i + w, cnt - 1)];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const double2 *b = (const double2 *)(a.bbox + 4 * (long long)e[w]);
+            bx[w] = b[0];
+            by[w] = b[1];
+        }
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const bool in = (x >= bx[w].x) & (x <= bx[w].y) & (y >= by[w].x) & (y <= by[w].y);
+            if (in & (i + w < cnt)) m |= 1ull << (i + w);
+        }
+    }
+    return m;
+}
 
 // Candidates of each point: hash cell, then the closed box, then session
 // exclusion; ascending element ids (the cell lists are sorted).  First
@@ -384,41 +412,46 @@ __global__ __launch_bounds__(256) void k2_cand(Loc2 a)
     const double x = skip ? NAN : a.pts[2 * (long long)t];
     const double y = skip ? NAN : a.pts[2 * (long long)t + 1];
     int n = 0, naabb = 0, full = a.obb ? 0 : 1;
+    int e0 = -1;  // the first slot's element (not read back below)
     if (x >= a.g.lo[0] && x <= a.g.hi[0] && y >= a.g.lo[1] && y <= a.g.hi[1]) {
         const long long c = cell2(a.g, 0, x) + (long long)a.g.nc[0] * cell2(a.g, 1, y);
         const int ps = a.psess ? a.psess[t] : -1;
+        const int qb = a.cell_off[c], qe = a.cell_off[c + 1];
         for (int pass = a.obb ? 0 : 1; pass < 2 && n == 0; ++pass) {
-            for (int q = a.cell_off[c]; q < a.cell_off[c + 1] && n < a.MC; ++q) {
-                const int e = a.cell_el[q];
-                const double *b = a.bbox + 4 * (long long)e;
-                if (!(x >= b[0] && x <= b[1] && y >= b[2] && y <= b[3])) continue;
-                if (ps >= 0 && a.esess && a.esess[e] == ps) continue;
-                if (pass == 0) {
-                    ++naabb;
-                    const float *o = a.obb + 10 * (long long)e;
-                    const double d0 = x - (double)o[4], d1 = y - (double)o[5];
-                    const double u0 = fma((double)o[1], d1, (double)o[0] * d0);
-                    const double u1 = fma((double)o[3], d1, (double)o[2] * d0);
-                    if (!(u0 >= (double)o[6] && u0 <= (double)o[8] && u1 >= (double)o[7] &&
-                          u1 <= (double)o[9]))
-                        continue;
+            for (int q0 = qb; q0 < qe; q0 += 64) {
+                unsigned long long todo = cell_hits2(a, q0, min(qe - q0, 64), x, y);
+                while (todo != 0ull) {
+                    const int e = a.cell_el[q0 + __ffsll((long long)todo) - 1];
+                    todo &= todo - 1ull;
+                    if (ps >= 0 && a.esess && a.esess[e] == ps) continue;
+                    if (pass == 0) {
+                        ++naabb;
+                        const float *o = a.obb + 10 * (long long)e;
+                        const double d0 = x - (double)o[4], d1 = y - (double)o[5];
+                        const double u0 = fma((double)o[1], d1, (double)o[0] * d0);
+                        const double u1 = fma((double)o[3], d1, (double)o[2] * d0);
+                        if (!(u0 >= (double)o[6] && u0 <= (double)o[8] && u1 >= (double)o[7] &&
+                              u1 <= (double)o[9]))
+                            continue;
+                    }
+                    a.cand_el[(long long)n * a.M + t] = e;
+                    e0 = n == 0 ? e : e0;
+                    ++n;
                 }
-                a.cand_el[(long long)n * a.M + t] = e;
-                ++n;
             }
             if (pass == 1 || naabb == 0 || n == naabb) full = 1;
             if (pass == 0 && naabb == 0) break;
         }
     }
     // ranks in the elements from converged code (shared atomics for lanes
-    // on the same element)
-    int nmax = n;
+    // on the same element); few elements: by rank_few
+    int nmax = a.few ? 0 : n;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) nmax = max(nmax, __shfl_xor(nmax, o, kWave));
     for (int k = 0; k < nmax; ++k) {
         const bool act = k < n;
         const long long s = (long long)k * a.M + t;
-        const int e = act ? a.cand_el[s] : -1;
+        const int e = act ? (k == 0 ? e0 : a.cand_el[s]) : -1;
         const int r = wave_rank(a.elem_cnt, e, act);
         if (act) a.cand_pos[s] = r;
     }
@@ -1224,8 +1257,12 @@ extern "C" int findpts2(fp2_handle *h, int npts, const double *pts, const int *p
             a.redo = round == 0 ? h->redo : nullptr;
             a.only = round == 0 ? nullptr : h->redo;
             FP_HIP(fill_int(h->elem_cnt, 0, (long long)h->E + 1, s));
+            a.few = round == 0 && h->E <= kFewMax && n / kFewPoints >= h->E;
             k2_cand<<<pb, 256, 0, s>>>(a);
             FP_HIP(hipGetLastError());
+            if (a.few)
+                FP_HIP(rank_few(h->ncand, kCount2, h->cand_el, h->cand_pos, h->elem_cnt, n, h->M,
+                                h->E, s));
             FP_HIP(scan_units(h->elem_cnt, h->elem_off, h->units, h->E, kUnit2, h->scan_tmp, s));
             k2_scatter<<<pb, 256, 0, s>>>(a);
             FP_HIP(hipGetLastError());
@@ -1296,8 +1333,13 @@ extern "C" int findpts2_eval(fp2_handle *h, int npts, const int *code, const int
             }
             if (f0 == 0) {
                 FP_HIP(fill_int(h->elem_cnt, 0, (long long)h->E + 1, s));
-                k2_ev_count<<<pb, 256, 0, s>>>(a);
-                FP_HIP(hipGetLastError());
+                if (h->E <= kFewMax && h->E < n) {
+                    FP_HIP(count_few(a.code, a.el, h->ev_pos, h->elem_cnt, n, h->E, a.out_all,
+                                     npts, nfields, s));
+                } else {
+                    k2_ev_count<<<pb, 256, 0, s>>>(a);
+                    FP_HIP(hipGetLastError());
+                }
                 FP_HIP(scan_units(h->elem_cnt, h->elem_off, h->units, h->E, kUnitEval2, h->scan_tmp,
                                   s));
                 k2_ev_scatter<<<pb, 256, 0, s>>>(a);

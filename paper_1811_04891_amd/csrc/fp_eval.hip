@@ -142,8 +142,14 @@ constexpr int kUnitEvalMfma = 256;  // points of one element per work unit
 constexpr int kEvMfmaMaxN1 = 8;      // orders with the matrix-core kernel
 static_assert(kMixed32MaxN1 == kEvMfmaMaxN1, "binary32 interpolation is the matrix-core kernel's");
 // Smallest pass that takes the staged path: below it the grouping's launches
-// cost more than the scattered stores they avoid.
-constexpr int kEvStageMin = 1 << 18;
+// cost more than the scattered stores they avoid, and few elements (counted in
+// LDS) need no sort for their counts either.  Staged against direct in us, order 7:
+// 16384 elements, 300,000 points 114 / 62 (1 field), 270 / 217 (8 fields), 1e6
+// points 158 / 128, 393 / 378; 32768 elements, 2e6 points 228 / 222, 667 / 704, 4e6
+// 368 / 394, 1062 / 1241; 4096 elements, 1.5e6 points 178 / 110, 448 / 442; 512
+// elements, 3e6 points 293 / 204, 819 / 860.
+constexpr int kEvStageMin = 1 << 20;
+constexpr int kEvStageMinFew = 1 << 21;  // up to kFewMax elements
 // Wavefronts per SIMD the binary64 interpolation kernel with up to 5 fields
 // is held to: three (at most 168 registers; a few bytes of spills at order 7
 // with 5 fields, 12 % faster than two wavefronts on the large box); the
@@ -537,8 +543,8 @@ int run_eval(fp_handle *h, const Work &w, int npts, const int *code, const int *
             l1 = pool_event(h);
             FP_HIP(hipEventRecord(t0, s));
         }
-        // Staged path (matrix-core orders, passes of at least kEvStageMin
-        // points): points grouped by element with the two-level counting
+        // Staged path (matrix-core orders, passes of at least kEvStageMin or
+        // kEvStageMinFew points): points grouped by element with the two-level counting
         // sort, values staged in the grouping's bucket order and moved to the
         // output by k_ev_unstage.  The grouping's
         // transient arrays and the staged values live in the pair-results
@@ -548,7 +554,8 @@ int run_eval(fp_handle *h, const Work &w, int npts, const int *code, const int *
         bool plan_ok = false;
         const GroupPlan gp = group_plan(n, h->E, &plan_ok);
         const int nf_max = nfields < kMaxEvalFields ? nfields : kMaxEvalFields;
-        const bool staged = !small && h->n1 <= kEvMfmaMaxN1 && n >= kEvStageMin && plan_ok && w.ev_slot &&
+        const bool staged = !small && h->n1 <= kEvMfmaMaxN1 && plan_ok &&
+                            n >= (h->E <= kFewMax ? kEvStageMinFew : kEvStageMin) && w.ev_slot &&
                             res_bytes >= group_transient_bytes(gp) &&
                             res_bytes >= (size_t)n * nf_max * sizeof(double);
         for (int f0 = 0; f0 < nfields; f0 += kMaxEvalFields) {
@@ -592,8 +599,13 @@ int run_eval(fp_handle *h, const Work &w, int npts, const int *code, const int *
                     FP_HIP(list_units(w.ev_off, w.ev_units, h->E, K, gb.scan_tmp, s));
                 } else {
                     FP_HIP(fill_int(w.ev_cnt, 0, (long long)h->E + 1, s));
-                    k_ev_count<<<pb, 256, 0, s>>>(a);
-                    FP_HIP(hipGetLastError());
+                    if (h->E <= kFewMax && h->E < n) {
+                        FP_HIP(count_few(a.code, a.el, w.ev_pos, w.ev_cnt, n, h->E, a.out_all,
+                                         npts, nfields, s));
+                    } else {
+                        k_ev_count<<<pb, 256, 0, s>>>(a);
+                        FP_HIP(hipGetLastError());
+                    }
                     FP_HIP(scan_units(w.ev_cnt, w.ev_off, w.ev_units, h->E, K, w.scan_tmp, s));
                     k_ev_scatter<<<pb, 256, 0, s>>>(a);
                     FP_HIP(hipGetLastError());

@@ -309,6 +309,28 @@ __device__ __forceinline__ int wave_rank(int *cnt, int e, bool act)
     return rank;
 }
 
+// Many entries of few elements: the counters of a grouping are then added to by
+// thousands of wavefronts each, one after the other (about 0.1 us per add to one
+// counter: counting 100,000 points in random order on 64 elements took 150 us).
+// Up to kFewMax elements (16 KB of LDS) blocks of a few thousand entries take their
+// ranks in LDS, with one add per block and element that occurs.  findpts ranks its
+// pairs so from kFewPoints points per element on (it costs a launch there, below
+// which the adds cost less: 4096 elements, order 7, 100,000 points 258 -> 263 us,
+// 1e6 points 1201 -> 1187), findpts_eval counts so whenever there are more points
+// than elements.  Locate / interpolation of 3 fields, order 7, before -> after:
+// 64 elements, 100,000 points 475 -> 287 us / 188 -> 41; 512 elements, 600,000
+// points 1094 -> 906 / 287 -> 112.
+constexpr int kFewMax = 4096;
+constexpr int kFewPoints = 64;
+// Ranks of the candidate pairs of n points in their elements, cnt counted up:
+// candidate k < (ncand[t] & mask) of point t is cand_el[k M + t].
+hipError_t rank_few(const int *ncand, int mask, const int *cand_el, int *cand_pos, int *cnt, int n,
+                    int M, int E, hipStream_t s);
+// Ranks of n located points in their elements (-1 and not a number in each of the
+// nf fields of out, stride apart, where a point was not found).
+hipError_t count_few(const int *code, const int *el, int *pos, int *cnt, int n, int E, double *out,
+                     long long stride, int nf, hipStream_t s);
+
 // Exclusive scan of n ints: out[0..n], out[n] = total.  tmp needs
 // scan_tmp_size(n) ints.  With gate non-null the kernels do nothing while
 // *gate is zero (a pass with no work), as does the gated fill.

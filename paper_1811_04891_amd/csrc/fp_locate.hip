@@ -54,6 +54,7 @@ struct LocArgs {
     int *elem_cnt;
     const int *elem_off;
     const UnitRec *units;  // work units of the pairs
+    bool few;              // rank_few ranks the pairs
     int E;
     int *order;
     double *res;
@@ -226,7 +227,7 @@ __global__ __launch_bounds__(256) void k_cand(LocArgs a)
             k < n && (k >= n1st || a.res_in[s] == kUnsolved || a.res_in[s] == kOutside);
         int e = -1;
         if (act) e = (k == 0 && e0 >= 0) ? e0 : ((k == 1 && e1 >= 0) ? e1 : a.cand_el[s]);
-        const int r = wave_rank(a.elem_cnt, e, act);
+        const int r = a.few ? 0 : wave_rank(a.elem_cnt, e, act);
         if (k < n) a.cand_pos[s] = act ? r : -1;
     }
     if (a.first) {  // the method's candidates of this block (first pass covers every point)
@@ -935,9 +936,13 @@ int run_findpts(fp_handle *h, const Work &w, int npts, const double *pts, const 
             continue;
         }
         const int K = unit_pairs(h, n);
+        a.few = h->E <= kFewMax && n / kFewPoints >= h->E;
         FP_HIP(fill_int(w.elem_cnt, 0, (long long)h->E + 1, s));
         k_cand<<<pb, 256, 0, s>>>(a);
         FP_HIP(hipGetLastError());
+        if (a.few)
+            FP_HIP(rank_few(w.ncand, kCountMask, w.cand_el, w.cand_pos, w.elem_cnt, n, w.M, h->E,
+                            s));
         FP_HIP(scan_units(w.elem_cnt, w.elem_off, w.units, h->E, K, w.scan_tmp, s));
         k_scatter<<<pb, 256, 0, s>>>(a);
         FP_HIP(hipGetLastError());
@@ -951,7 +956,7 @@ int run_findpts(fp_handle *h, const Work &w, int npts, const double *pts, const 
         FP_HIP(hipGetLastError());
         // second pass over the flagged tasks with the axis-aligned candidates
         // only (other tasks get no candidates and keep their result)
-        a.first = false;
+        a.first = a.few = false;
         a.redo = nullptr;
         a.only = w.redo;
         a.pair_max = kPairMax;

@@ -207,6 +207,95 @@ hipError_t list_units(const int *off, UnitRec *units, int E, int K, int *tmp, hi
         ScanArgs{off, E, K, nullptr, nullptr, units, nullptr}, tmp, s);
 }
 
+constexpr int kFewThreads = 1024;
+
+// Entries per block of few-element ranks.
+static int few_chunk(int n)
+{
+    const int c = n / 256 / kFewThreads * kFewThreads;
+    return c < kFewThreads ? kFewThreads : (c > 8 * kFewThreads ? 8 * kFewThreads : c);
+}
+
+// The block's entries counted in c: from here on c[e] is their base in element e.
+__device__ __forceinline__ void few_bases(int *c, int *__restrict__ cnt, int E)
+{
+    __syncthreads();
+    for (int e = threadIdx.x; e < E; e += kFewThreads)
+        if (c[e]) c[e] = atomicAdd(&cnt[e], c[e]);
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(kFewThreads) void k_rank_few(const int *__restrict__ ncand, int mask,
+                                                          const int *__restrict__ cand_el,
+                                                          int *cand_pos, int *__restrict__ cnt,
+                                                          int npts, int M, int E, int chunk)
+{
+    __shared__ int c[kFewMax];
+    for (int e = threadIdx.x; e < E; e += kFewThreads) c[e] = 0;
+    __syncthreads();
+    const int beg = blockIdx.x * chunk, end = min(beg + chunk, npts);
+    for (int t = beg + (int)threadIdx.x; t < end; t += kFewThreads) {
+        const int n = ncand[t] & mask;
+        for (int k = 0; k < n; ++k) {
+            const long long s = (long long)k * M + t;
+            cand_pos[s] = atomicAdd(&c[cand_el[s]], 1);
+        }
+    }
+    few_bases(c, cnt, E);
+    for (int t = beg + (int)threadIdx.x; t < end; t += kFewThreads) {
+        const int n = ncand[t] & mask;
+        for (int k = 0; k < n; ++k) {
+            const long long s = (long long)k * M + t;
+            cand_pos[s] += c[cand_el[s]];
+        }
+    }
+}
+
+__global__ __launch_bounds__(kFewThreads) void k_count_few(const int *__restrict__ code,
+                                                           const int *__restrict__ el, int *pos,
+                                                           int *__restrict__ cnt, int n, int E,
+                                                           double *__restrict__ out,
+                                                           long long stride, int nf, int chunk)
+{
+    __shared__ int c[kFewMax];
+    for (int e = threadIdx.x; e < E; e += kFewThreads) c[e] = 0;
+    __syncthreads();
+    const int beg = blockIdx.x * chunk, end = min(beg + chunk, n);
+    const auto key = [&](int p) {
+        const int e = el[p];
+        return code[p] != FP_NOT_FOUND && e >= 0 && e < E ? e : -1;
+    };
+    for (int p = beg + (int)threadIdx.x; p < end; p += kFewThreads) {
+        const int e = key(p);
+        pos[p] = e < 0 ? -1 : atomicAdd(&c[e], 1);
+        if (e < 0)
+            for (int f = 0; f < nf; ++f) out[f * stride + p] = NAN;
+    }
+    few_bases(c, cnt, E);
+    for (int p = beg + (int)threadIdx.x; p < end; p += kFewThreads) {
+        const int e = key(p);
+        if (e >= 0) pos[p] += c[e];
+    }
+}
+
+hipError_t rank_few(const int *ncand, int mask, const int *cand_el, int *cand_pos, int *cnt, int n,
+                    int M, int E, hipStream_t s)
+{
+    const int chunk = few_chunk(n);
+    k_rank_few<<<(n + chunk - 1) / chunk, kFewThreads, 0, s>>>(ncand, mask, cand_el, cand_pos, cnt,
+                                                               n, M, E, chunk);
+    return hipGetLastError();
+}
+
+hipError_t count_few(const int *code, const int *el, int *pos, int *cnt, int n, int E, double *out,
+                     long long stride, int nf, hipStream_t s)
+{
+    const int chunk = few_chunk(n);
+    k_count_few<<<(n + chunk - 1) / chunk, kFewThreads, 0, s>>>(code, el, pos, cnt, n, E, out,
+                                                                stride, nf, chunk);
+    return hipGetLastError();
+}
+
 __global__ void k_fill_int(int *__restrict__ p, int v, long long n, const int *__restrict__ gate)
 {
     if (gate && !*gate) return;

@@ -66,6 +66,28 @@ def test_both_paths_match_oracle(N):
     h.free()
 
 
+@pytest.mark.parametrize("shape", [(1, 8), (16, 64), (41, 100)])
+def test_crowded_and_many_elements(shape):
+    """A grouped call on few elements (ranks in LDS) and just past their limit."""
+    from paper_1811_04891_amd import findpts as fp
+    print(f"case: 2D grouped call on {shape}", flush=True)
+    dev = torch.device("cuda:0")
+    m = w.annulus2d_mesh(*shape, N=3)
+    n = LIMIT + 2049
+    pts = _points(n, 11)
+    md = m.to(dev)
+    h = fp.findpts2_setup(md.x, md.y, 3, tol=TOL, max_points=n)
+    fields = [m.x * m.y, m.y]
+    res, out = _call(fp, h, torch.as_tensor(pts).to(dev), None, [f.to(dev) for f in fields])
+    om = oracle.OracleMesh2.from_mesh(m, TOL)
+    _, hs = om.bbox()
+    sub = np.arange(0, n, 16)
+    compare_locate(om, pts[sub], [a[sub] for a in res], om.findpts(pts[sub]), hs, TOL)
+    hf = [f.numpy() for f in fields]
+    compare_eval(out, om.eval(res[0], res[1], res[2], hf), hf)
+    h.free()
+
+
 @pytest.mark.parametrize("N", [1, 4, 7, 11])
 @pytest.mark.parametrize("nf", [1, 9])
 def test_small_call_sessions_and_field_counts(N, nf):

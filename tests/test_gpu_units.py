@@ -71,3 +71,31 @@ def test_units_of_all_sizes(N, shape):
     torch.cuda.synchronize()
     compare_eval(out2.cpu().numpy(), exp, hf)
     h.free()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("shape,n", [((4, 4, 4), (1 << 21) + 37), ((17, 16, 16), (1 << 20) + 37)])
+def test_staged_and_direct_interpolation_agree(shape, n, prec):
+    """A pass just past the staged path's smallest (few and many elements) and
+    the same points in two direct calls: identical bytes, not-found included."""
+    from paper_1811_04891_amd import findpts as fp
+    print(f"case: staged and direct interpolation, {shape}, {n} points, {prec}", flush=True)
+    dev = torch.device("cuda:0")
+    m = w.box_mesh(*shape, N=3).to(dev)
+    fields = [m.x * m.y, m.z - 0.5 * m.x]
+    g = torch.Generator(device=dev).manual_seed(3)
+    code = torch.zeros(n, dtype=torch.int32, device=dev)
+    code[::7] = 2
+    el = torch.randint(0, m.E, (n,), generator=g, device=dev, dtype=torch.int32)
+    rst = 2.0 * torch.rand((n, 3), generator=g, device=dev, dtype=torch.float64) - 1.0
+    h = fp.findpts_setup(m.x, m.y, m.z, 3, tol=TOL, max_points=n,
+                         precision=fp.FP_PREC_MIXED if prec == "mixed" else fp.FP_PREC_FP64)
+    whole = fp.findpts_eval(h, code, el, rst, fields)
+    cut = n // 2
+    parts = [fp.findpts_eval(h, code[a:b].contiguous(), el[a:b].contiguous(),
+                             rst[a:b].contiguous(), fields) for a, b in ((0, cut), (cut, n))]
+    torch.cuda.synchronize()
+    both = torch.cat(parts, dim=1)
+    assert torch.equal(whole.view(torch.int64)[:, code == 0], both.view(torch.int64)[:, code == 0])
+    assert torch.isnan(whole[:, code == 2]).all() and torch.isnan(both[:, code == 2]).all()
+    h.free()
