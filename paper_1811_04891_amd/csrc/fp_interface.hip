@@ -17,12 +17,37 @@ constexpr int kFluxBlocks = 256;
 constexpr int kFluxThreads = 256;
 static_assert(2 * kFluxBlocks + 1 <= FP_FLUX_WORK, "flux workspace");
 
+// The block's sums of f and ar, in thread 0: halving steps, thread t adding thread
+// t + o's value, through LDS until one wavefront is left.
+__device__ __forceinline__ void flux_sums(double &f, double &ar)
+{
+    __shared__ double sf[kFluxThreads / 2], sa[kFluxThreads / 2];
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int o = kFluxThreads / 2; o >= kWave; o >>= 1) {
+        if (t >= o && t < 2 * o) {
+            sf[t - o] = f;
+            sa[t - o] = ar;
+        }
+        __syncthreads();
+        if (t < o) {
+            f += sf[t];
+            ar += sa[t];
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        f += __shfl_down(f, o, kWave);
+        ar += __shfl_down(ar, o, kWave);
+    }
+}
+
 __global__ __launch_bounds__(kFluxThreads) void k_flux_partial(
     int npts, const double *__restrict__ w, const double *__restrict__ n, long long ldn,
     const int *__restrict__ iface, const double *__restrict__ u, long long ldu,
     double *__restrict__ part)
 {
-    __shared__ double sf[kFluxThreads], sa[kFluxThreads];
     double f = 0.0, ar = 0.0;
     for (long long p = (long long)blockIdx.x * kFluxThreads + threadIdx.x; p < npts;
          p += (long long)kFluxBlocks * kFluxThreads) {
@@ -31,49 +56,41 @@ __global__ __launch_bounds__(kFluxThreads) void k_flux_partial(
         f = fma(w[p], un, f);
         if (!iface || iface[p]) ar = fma(w[p], fma(n2, n2, fma(n1, n1, n0 * n0)), ar);
     }
-    sf[threadIdx.x] = f;
-    sa[threadIdx.x] = ar;
-    __syncthreads();
-    for (int o = kFluxThreads / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) {
-            sf[threadIdx.x] += sf[threadIdx.x + o];
-            sa[threadIdx.x] += sa[threadIdx.x + o];
-        }
-        __syncthreads();
-    }
+    flux_sums(f, ar);
     if (threadIdx.x == 0) {
-        part[1 + blockIdx.x] = sf[0];
-        part[1 + kFluxBlocks + blockIdx.x] = sa[0];
+        part[1 + blockIdx.x] = f;
+        part[1 + kFluxBlocks + blockIdx.x] = ar;
     }
 }
 
-__global__ __launch_bounds__(kFluxBlocks) void k_flux_gamma(double *__restrict__ work)
+// gamma from the partial sums, by every block for itself (4 KB from its L2: a
+// launch between the two kernels for it made the eight corrections of an exchange
+// step 10 us slower, 300 -> 290 us), and the correction of the block's points.
+constexpr int kFluxApplyBlocks = 2048;
+__global__ __launch_bounds__(kFluxThreads) void k_flux_apply(int npts,
+                                                             const double *__restrict__ n,
+                                                             long long ldn,
+                                                             const int *__restrict__ iface,
+                                                             double *__restrict__ u, long long ldu,
+                                                             double *__restrict__ work)
 {
-    __shared__ double sf[kFluxBlocks], sa[kFluxBlocks];
-    sf[threadIdx.x] = work[1 + threadIdx.x];
-    sa[threadIdx.x] = work[1 + kFluxBlocks + threadIdx.x];
+    static_assert(kFluxBlocks == kFluxThreads, "one partial sum per thread");
+    __shared__ double gamma;
+    double f = work[1 + threadIdx.x], ar = work[1 + kFluxBlocks + threadIdx.x];
+    flux_sums(f, ar);
+    if (threadIdx.x == 0) {
+        gamma = ar > 0.0 ? -f / ar : 0.0;
+        if (blockIdx.x == 0) work[0] = gamma;
+    }
     __syncthreads();
-    for (int o = kFluxBlocks / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) {
-            sf[threadIdx.x] += sf[threadIdx.x + o];
-            sa[threadIdx.x] += sa[threadIdx.x + o];
-        }
-        __syncthreads();
+    const double g = gamma;
+    for (long long p = (long long)blockIdx.x * kFluxThreads + threadIdx.x; p < npts;
+         p += (long long)gridDim.x * kFluxThreads) {
+        if (iface && !iface[p]) continue;
+        u[p] = fma(g, n[p], u[p]);
+        u[ldu + p] = fma(g, n[ldn + p], u[ldu + p]);
+        u[2 * ldu + p] = fma(g, n[2 * ldn + p], u[2 * ldu + p]);
     }
-    if (threadIdx.x == 0) work[0] = sa[0] > 0.0 ? -sf[0] / sa[0] : 0.0;
-}
-
-__global__ __launch_bounds__(256) void k_flux_apply(int npts, const double *__restrict__ n,
-                                                    long long ldn, const int *__restrict__ iface,
-                                                    double *__restrict__ u, long long ldu,
-                                                    const double *__restrict__ work)
-{
-    const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= npts || (iface && !iface[p])) return;
-    const double g = work[0];
-    u[p] = fma(g, n[p], u[p]);
-    u[ldu + p] = fma(g, n[ldn + p], u[ldu + p]);
-    u[2 * ldu + p] = fma(g, n[2 * ldn + p], u[2 * ldu + p]);
 }
 
 struct ExtArgs {
@@ -108,12 +125,10 @@ extern "C" int fp_flux_correct(int npts, const double *w, const double *n, long 
     hipStream_t s = (hipStream_t)stream;
     k_flux_partial<<<kFluxBlocks, kFluxThreads, 0, s>>>(npts, w, n, ldn, iface, u, ldu, work);
     FP_HIP(hipGetLastError());
-    k_flux_gamma<<<1, kFluxBlocks, 0, s>>>(work);
+    const int nblk = npts / kFluxThreads + 1;
+    k_flux_apply<<<nblk < kFluxApplyBlocks ? nblk : kFluxApplyBlocks, kFluxThreads, 0, s>>>(
+        npts, n, ldn, iface, u, ldu, work);
     FP_HIP(hipGetLastError());
-    if (npts > 0) {
-        k_flux_apply<<<(npts + 255) / 256, 256, 0, s>>>(npts, n, ldn, iface, u, ldu, work);
-        FP_HIP(hipGetLastError());
-    }
     return FP_OK;
 }
 
