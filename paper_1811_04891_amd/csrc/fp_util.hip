@@ -18,20 +18,20 @@ int hip_fail(hipError_t e, const char *what)
 }
 
 // ---------------------------------------------------------------------------
-// Exclusive scans, tiles of 256 threads x 4 items: one launch for one tile, else
-// the tile sums, then each block adds up the sums before its own and scans its
-// tile.  A pass groups its pairs and its points with these, in a chain where a
-// launch costs 4 to 5 us whatever it does: the 16384 elements of the annulus took
-// 15 us in three launches (the sums scanned by one of their own), and take 9.
-// Measured against: one launch where each block adds up all items before its tile
-// (25 us), and one block for all of them (50 us: its stores go through one CU).
+// Exclusive scans, tiles of 256 threads x 4 items (16 in lists of more than 2^20,
+// whose tile sums would be many): one launch for one tile, else the tile sums, then
+// each block adds up the sums before its own and scans its tile.  A pass groups its
+// pairs and its points with these, in a chain where a launch costs 4 to 5 us
+// whatever it does: the 16384 elements of the annulus took 15 us in three launches
+// (the sums scanned by one of their own), and take 9.  Measured against: one launch
+// where each block adds up all items before its tile (25 us), and one block for all
+// of them (50 us: its stores go through one CU).
 //
 // Groupings also get their work units: the sums then carry the entries in the
 // low and the units in the high 32 bits.
 // ---------------------------------------------------------------------------
 constexpr int kScanThreads = 256;
-constexpr int kScanItems = 4;
-constexpr int kScanTile = kScanThreads * kScanItems;
+constexpr int scan_items(long long n) { return n > (1 << 20) ? 16 : 4; }
 typedef unsigned long long u64;
 
 // Block-wide exclusive scan of one value per thread; returns the thread's
@@ -83,58 +83,58 @@ __device__ __forceinline__ u64 scan_value(int cnt, int K)
 }
 
 // The thread's consecutive counts from item i0 (zero past the last).
-template <ScanMode MODE>
-__device__ __forceinline__ void scan_load(const ScanArgs &a, long long i0, int (&v)[kScanItems])
+template <ScanMode MODE, int ITEMS>
+__device__ __forceinline__ void scan_load(const ScanArgs &a, long long i0, int (&v)[ITEMS])
 {
-    constexpr int L = MODE == kOffsets ? kScanItems + 1 : kScanItems;
+    constexpr int L = MODE == kOffsets ? ITEMS + 1 : ITEMS;
     const long long m = MODE == kOffsets ? (long long)a.n : (long long)a.n - 1;
     int w[L];
 #pragma unroll
     for (int k = 0; k < L; ++k) w[k] = a.in[i0 + k < m ? i0 + k : m];
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k)
+    for (int k = 0; k < ITEMS; ++k)
         v[k] = i0 + k >= a.n ? 0 : (MODE == kOffsets ? w[(k + 1) % L] - w[k] : w[k]);
 }
 
-template <ScanMode MODE>
+template <ScanMode MODE, int ITEMS>
 __device__ __forceinline__ u64 scan_sum(const ScanArgs &a, long long i0)
 {
-    int v[kScanItems];
-    scan_load<MODE>(a, i0, v);
+    int v[ITEMS];
+    scan_load<MODE, ITEMS>(a, i0, v);
     u64 s = 0;
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) s += scan_value<MODE>(v[k], a.K);
+    for (int k = 0; k < ITEMS; ++k) s += scan_value<MODE>(v[k], a.K);
     return s;
 }
 
-template <ScanMode MODE>
+template <ScanMode MODE, int ITEMS>
 __global__ __launch_bounds__(kScanThreads) void k_scan_tiles(ScanArgs a)
 {
     if (a.gate && !*a.gate) return;
     u64 tot;
-    block_excl_scan(scan_sum<MODE>(a, (long long)blockIdx.x * kScanTile + threadIdx.x * kScanItems),
+    block_excl_scan(scan_sum<MODE, ITEMS>(a, (long long)blockIdx.x * (kScanThreads * ITEMS) + threadIdx.x * ITEMS),
                     &tot);
     if (threadIdx.x == 0) a.tsum[blockIdx.x] = tot;
 }
 
-template <ScanMode MODE>
+template <ScanMode MODE, int ITEMS>
 __global__ __launch_bounds__(kScanThreads) void k_scan(ScanArgs a)
 {
     if (a.gate && !*a.gate) return;
-    const long long i0 = (long long)blockIdx.x * kScanTile + threadIdx.x * kScanItems;
-    int v[kScanItems];
-    scan_load<MODE>(a, i0, v);
+    const long long i0 = (long long)blockIdx.x * (kScanThreads * ITEMS) + threadIdx.x * ITEMS;
+    int v[ITEMS];
+    scan_load<MODE, ITEMS>(a, i0, v);
     u64 s = 0, tot, run = 0;
     for (int t = threadIdx.x; t < (int)blockIdx.x; t += kScanThreads) s += a.tsum[t];
     if (blockIdx.x > 0) block_excl_scan(s, &run);
     s = 0;
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) s += scan_value<MODE>(v[k], a.K);
+    for (int k = 0; k < ITEMS; ++k) s += scan_value<MODE>(v[k], a.K);
     const u64 before = block_excl_scan(s, &tot);
     const u64 all = run + tot;
     run += before;
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
+    for (int k = 0; k < ITEMS; ++k) {
         const long long i = i0 + k;
         const int beg = (int)(unsigned)run;
         if (MODE != kOffsets && i < a.n) a.out[i] = beg;
@@ -169,18 +169,34 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(ScanArgs a)
     }
 }
 
-// Ints of the tile sums.
-int scan_tmp_size(long long n) { return 2 * (int)((n + kScanTile - 1) / kScanTile) + 2; }
+static int scan_tiles(long long n)
+{
+    const int tile = kScanThreads * scan_items(n);
+    return (int)((n + tile - 1) / tile);
+}
+
+// Ints of the tile sums of a scan of at most n items (a list of 2^20 has as many
+// tiles as one four times as long).
+int scan_tmp_size(long long n)
+{
+    const int small = scan_tiles(n < (1 << 20) ? n : (1 << 20)), own = scan_tiles(n);
+    return 2 * (small > own ? small : own) + 2;
+}
 
 __global__ void k_zero_total(int *out, int n) { out[n] = 0; }
 
 template <ScanMode MODE>
 static hipError_t launch_scan(ScanArgs a, int *tmp, hipStream_t s)
 {
-    const int nt = (a.n + kScanTile - 1) / kScanTile;
+    const int nt = scan_tiles(a.n);
     a.tsum = (u64 *)tmp;
-    if (nt > 1) k_scan_tiles<MODE><<<nt, kScanThreads, 0, s>>>(a);
-    k_scan<MODE><<<nt, kScanThreads, 0, s>>>(a);
+    if (scan_items(a.n) == 4) {
+        if (nt > 1) k_scan_tiles<MODE, 4><<<nt, kScanThreads, 0, s>>>(a);
+        k_scan<MODE, 4><<<nt, kScanThreads, 0, s>>>(a);
+    } else {
+        k_scan_tiles<MODE, 16><<<nt, kScanThreads, 0, s>>>(a);
+        k_scan<MODE, 16><<<nt, kScanThreads, 0, s>>>(a);
+    }
     return hipGetLastError();
 }
 

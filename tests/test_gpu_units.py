@@ -99,3 +99,31 @@ def test_staged_and_direct_interpolation_agree(shape, n, prec):
     assert torch.equal(whole.view(torch.int64)[:, code == 0], both.view(torch.int64)[:, code == 0])
     assert torch.isnan(whole[:, code == 2]).all() and torch.isnan(both[:, code == 2]).all()
     h.free()
+
+
+def test_more_elements_than_a_large_scan_tile_switch():
+    """Over 2^20 elements (the scans then take larger tiles): known owners and a
+    linear field, through both interpolation entry points."""
+    from paper_1811_04891_amd import findpts as fp
+    print("case: 1,100,000 elements of order 1", flush=True)
+    dev = torch.device("cuda:0")
+    m = w.box_mesh(110, 100, 100, N=1)
+    rng = np.random.default_rng(2)
+    own = np.concatenate([rng.integers(0, m.E, 30000), np.full(700, m.E - 1), np.full(300, 0)])
+    X = np.stack([m.x.numpy(), m.y.numpy(), m.z.numpy()], 1).reshape(m.E, 3, -1)[own]
+    pts = X.min(2) + (X.max(2) - X.min(2)) * rng.uniform(0.05, 0.95, (len(own), 3))
+    md = m.to(dev)
+    h = fp.findpts_setup(md.x, md.y, md.z, 1, tol=TOL, max_points=len(own))
+    dp = torch.as_tensor(pts).to(dev)
+    code, el, rst, _ = fp.findpts(h, dp)
+    f = [(md.x + 2.0 * md.y - md.z).contiguous()]
+    out = fp.findpts_eval(h, code, el, rst, f)
+    out2 = torch.empty_like(out)
+    fp.findpts_eval_noalloc(h, code, el, rst, f, out2)
+    torch.cuda.synchronize()
+    assert torch.all(code == 0) and np.array_equal(el.cpu().numpy(), own)
+    exact = dp[:, 0] + 2.0 * dp[:, 1] - dp[:, 2]
+    # r is found to 1e-12 of an element of at most 0.01; sums of a few terms of at most 3
+    assert torch.max(torch.abs(out[0] - exact)) <= 1e-13
+    assert torch.equal(out, out2)
+    h.free()
