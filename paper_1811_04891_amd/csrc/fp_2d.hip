@@ -376,7 +376,7 @@ struct Loc2 {
 
 // Entries q0 .. q0 + cnt - 1 (at most 64) of the cell lists whose box holds
 // (x, y), four loaded at a time: taken one by one, a wavefront waited on its
-// lists entry by entry (k2_cand on 1.01e6 points of the ring 131 us, 66 now).
+// lists entry by entry (k2_cand on 1.01e6 points of the ring 131 us, 95 now).
 __device__ __forceinline__ unsigned long long cell_hits2(const Loc2 &a, int q0, int cnt, double x,
                                                          double y)
 {
