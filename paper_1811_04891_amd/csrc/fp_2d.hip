@@ -474,6 +474,9 @@ __global__ __launch_bounds__(256) void k2_cand(Loc2 a)
 __global__ __launch_bounds__(256) void k2_scatter(Loc2 a)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    // the counts are in the offsets by now: cleared here for the second round
+    if (a.obb)
+        for (int e = t; e < a.E; e += gridDim.x * blockDim.x) a.elem_cnt[e] = 0;
     if (t >= a.npts) return;
     const int n = a.ncand[t] & kCount2;
     for (int k = 0; k < n; ++k) {
@@ -731,16 +734,59 @@ __global__ __launch_bounds__(kWave) void k2_locate(Loc2 a, const double *__restr
     if (threadIdx.x == 0) a.iter_part[blockIdx.x] = (unsigned)my_iters;
 }
 
+// A round's partial counts, folded into the handle's counters by the first
+// kStats2Blocks blocks of its k2_select (a launch of its own cost 8 us in each round).
+constexpr int kStats2Blocks = 16;
+struct Stat2Args {
+    int ni, nb;  // partial counts: Newton blocks, k2_cand blocks
+    unsigned long long *stats;
+};
+
+__device__ __forceinline__ void fold_stats2(const Loc2 &a, const Stat2Args &q)
+{
+    constexpr int T = 256;
+    __shared__ unsigned long long si[T / kWave], sc[T / kWave];
+    unsigned long long it = 0, c = 0;
+    const int i0 = blockIdx.x * T + threadIdx.x;
+    for (int i = i0; i < q.ni; i += kStats2Blocks * T) it += a.iter_part[i];
+    for (int i = i0; i < q.nb; i += kStats2Blocks * T) c += a.cand_part[i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        it += __shfl_xor(it, o, kWave);
+        c += __shfl_xor(c, o, kWave);
+    }
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        si[threadIdx.x / kWave] = it;
+        sc[threadIdx.x / kWave] = c;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long I = 0, Cn = 0;
+        for (int w = 0; w < T / kWave; ++w) {
+            I += si[w];
+            Cn += sc[w];
+        }
+        if (blockIdx.x == 0) atomicAdd(&q.stats[0], (unsigned long long)a.elem_off[a.E]);
+        if (I) atomicAdd(&q.stats[1], I);
+        if (Cn) atomicAdd(&q.stats[2], Cn);
+    }
+}
+
 // Owner selection per point (candidates in ascending element order): an
 // inside candidate wins (with a distance field: the session whose best
 // inside value is largest, ties to the smaller session, then the smallest
 // element of it; else the smallest element); otherwise the smallest distance
 // (ties within 1e-14 relative keep the smaller id); no candidate: not found.
-__global__ __launch_bounds__(256) void k2_select(Loc2 a, int *__restrict__ code,
+__global__ __launch_bounds__(256) void k2_select(Loc2 a, Stat2Args q,
+                                                 int *__restrict__ code,
                                                  int *__restrict__ el, double *__restrict__ rs,
                                                  double *__restrict__ dist2)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (blockIdx.x < kStats2Blocks) {
+        fold_stats2(a, q);
+        return;
+    }
+    const int t = (blockIdx.x - kStats2Blocks) * blockDim.x + threadIdx.x;
     if (t >= a.npts || (a.only && !a.only[t])) return;  // second round: flagged points
     const int nv = a.ncand[t];
     const int n = nv & kCount2;
@@ -801,36 +847,6 @@ __global__ __launch_bounds__(256) void k2_select(Loc2 a, int *__restrict__ code,
         dist2[t] = o[2];
     }
     if (a.obb) a.redo[t] = (c != 0 && !full) ? 1 : 0;
-}
-
-__global__ __launch_bounds__(1024) void k2_stats(const unsigned *iter_part, int ni,
-                                                 const unsigned *cand_part, int nb, int E,
-                                                 const int *elem_off, unsigned long long *stats)
-{
-    __shared__ unsigned long long si[1024 / kWave], sc[1024 / kWave];
-    unsigned long long it = 0, c = 0;
-    for (int i = threadIdx.x; i < ni; i += blockDim.x) it += iter_part[i];
-    for (int i = threadIdx.x; i < nb; i += blockDim.x) c += cand_part[i];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        it += __shfl_xor(it, o, kWave);
-        c += __shfl_xor(c, o, kWave);
-    }
-    if ((threadIdx.x & (kWave - 1)) == 0) {
-        si[threadIdx.x / kWave] = it;
-        sc[threadIdx.x / kWave] = c;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long I = 0, Cn = 0;
-        for (int w = 0; w < (int)(blockDim.x / kWave); ++w) {
-            I += si[w];
-            Cn += sc[w];
-        }
-        atomicAdd(&stats[0], (unsigned long long)elem_off[E]);
-        atomicAdd(&stats[1], I);
-        if (Cn) atomicAdd(&stats[2], Cn);
-    }
 }
 
 // ---- interpolation -------------------------------------------------------
@@ -1256,7 +1272,7 @@ extern "C" int findpts2(fp2_handle *h, int npts, const double *pts, const int *p
             a.obb = round == 0 ? h->obb : nullptr;
             a.redo = round == 0 ? h->redo : nullptr;
             a.only = round == 0 ? nullptr : h->redo;
-            FP_HIP(fill_int(h->elem_cnt, 0, (long long)h->E + 1, s));
+            if (round == 0) FP_HIP(fill_int(h->elem_cnt, 0, (long long)h->E + 1, s));
             a.few = round == 0 && h->E <= kFewMax && n / kFewPoints >= h->E;
             k2_cand<<<pb, 256, 0, s>>>(a);
             FP_HIP(hipGetLastError());
@@ -1268,11 +1284,9 @@ extern "C" int findpts2(fp2_handle *h, int npts, const double *pts, const int *p
             FP_HIP(hipGetLastError());
             const int nblk = unit_grid(h->E, n, kUnit2);
             FP_HIP(launch_locate2(h, a, nblk, s));
-            k2_select<<<pb, 256, 0, s>>>(a, code + start, el + start, rs + 2 * (long long)start,
-                                         dist2 + start);
-            FP_HIP(hipGetLastError());
-            k2_stats<<<1, 1024, 0, s>>>(h->iter_part, nblk, h->cand_part, round == 0 ? pb : 0,
-                                        h->E, h->elem_off, h->stats);
+            k2_select<<<kStats2Blocks + pb, 256, 0, s>>>(
+                a, Stat2Args{nblk, round == 0 ? pb : 0, h->stats}, code + start, el + start,
+                rs + 2 * (long long)start, dist2 + start);
             FP_HIP(hipGetLastError());
         }
     }

@@ -333,7 +333,7 @@ hipError_t count_few(const int *code, const int *el, int *pos, int *cnt, int n, 
 
 // Exclusive scan of n ints: out[0..n], out[n] = total.  tmp needs
 // scan_tmp_size(n) ints.  With gate non-null the kernels do nothing while
-// *gate is zero (a pass with no work), as does the gated fill.
+// *gate is zero (a pass with no work).
 int scan_tmp_size(long long n);
 hipError_t scan_exclusive(const int *in, int *out, int n, int *tmp,
                           hipStream_t s, const int *gate = nullptr);
@@ -343,7 +343,6 @@ hipError_t scan_units(const int *cnt, int *off, UnitRec *units, int E, int K, in
                       const int *gate = nullptr);
 // The unit list of offsets that are already there.
 hipError_t list_units(const int *off, UnitRec *units, int E, int K, int *tmp, hipStream_t s);
-hipError_t fill_int_gated(int *p, int value, long long n, const int *gate, hipStream_t s);
 
 // GLL nodes and barycentric weights of order N; the inverse of the
 // Bernstein-to-nodal matrix (n1 x n1, row-major), both computed on the host.

@@ -249,6 +249,9 @@ __global__ __launch_bounds__(256) void k_scatter(LocArgs a)
 {
     if (a.only && !*a.gate) return;
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    // the counts are in the offsets by now: cleared here for the second pass
+    if (a.first)
+        for (int e = p; e < a.E; e += gridDim.x * blockDim.x) a.elem_cnt[e] = 0;
     if (p >= a.npts) return;
     const int n = a.ncand[p] & kCountMask;  // 0 for tasks the pass skips
     for (int k = 0; k < n; ++k) {
@@ -518,20 +521,24 @@ __device__ __forceinline__ void store_pair(const LocArgs &a, int slot, const TRN
 
 constexpr int kStatsBlocks = 32;
 
-// Fold one pass's partial counts into the handle's counters: a few blocks,
-// each adding its share with one atomic per counter.
-__global__ __launch_bounds__(1024) void k_stats(const unsigned *cand_part, int nb,
-                                                const unsigned *iter_part, int ni, int E,
-                                                const int *elem_off, long long located,
-                                                int first, const int *gate,
-                                                unsigned long long *stats)
+// One pass's partial counts, folded into the handle's counters by the first
+// kStatsBlocks blocks of its k_select, each adding its share with one atomic per
+// counter (a launch of its own cost 4.5 us in each pass).
+struct StatArgs {
+    const unsigned *cand_part, *iter_part;
+    int nb, ni;         // partial counts of each
+    long long located;  // points of the pass
+    unsigned long long *stats;
+};
+
+__device__ __forceinline__ void fold_stats(const LocArgs &a, const StatArgs &q)
 {
-    if (gate && !*gate) return;
-    __shared__ unsigned long long sc[1024 / kWave], si[1024 / kWave];
+    constexpr int T = 256;
+    __shared__ unsigned long long sc[T / kWave], si[T / kWave];
     unsigned long long c = 0, it = 0;
-    const int stride = blockDim.x * gridDim.x;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nb; i += stride) c += cand_part[i];
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < ni; i += stride) it += iter_part[i];
+    const int i0 = blockIdx.x * T + threadIdx.x;
+    for (int i = i0; i < q.nb; i += kStatsBlocks * T) c += q.cand_part[i];
+    for (int i = i0; i < q.ni; i += kStatsBlocks * T) it += q.iter_part[i];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         c += __shfl_xor(c, o, kWave);
@@ -544,19 +551,20 @@ __global__ __launch_bounds__(1024) void k_stats(const unsigned *cand_part, int n
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned long long C = 0, I = 0;
-        for (int w = 0; w < (int)(blockDim.x / kWave); ++w) {
+        for (int w = 0; w < T / kWave; ++w) {
             C += sc[w];
             I += si[w];
         }
-        const unsigned long long pairs = blockIdx.x == 0 ? (unsigned long long)elem_off[E] : 0ull;
-        if (pairs) atomicAdd(&stats[0], pairs);
-        if (I) atomicAdd(&stats[1], I);
-        if (first) {
-            if (pairs) atomicAdd(&stats[4], pairs);
-            if (I) atomicAdd(&stats[5], I);
+        const unsigned long long pairs =
+            blockIdx.x == 0 ? (unsigned long long)a.elem_off[a.E] : 0ull;
+        if (pairs) atomicAdd(&q.stats[0], pairs);
+        if (I) atomicAdd(&q.stats[1], I);
+        if (a.first) {
+            if (pairs) atomicAdd(&q.stats[4], pairs);
+            if (I) atomicAdd(&q.stats[5], I);
         }
-        if (located && blockIdx.x == 0) atomicAdd(&stats[2], (unsigned long long)located);
-        if (C) atomicAdd(&stats[3], C);
+        if (q.located && blockIdx.x == 0) atomicAdd(&q.stats[2], (unsigned long long)q.located);
+        if (C) atomicAdd(&q.stats[3], C);
     }
 }
 
@@ -598,13 +606,18 @@ __device__ __forceinline__ void select_delta(const LocArgs &a, BasisPtr<double> 
 // (the second pass appends the candidates the first dropped, unsorted).  N1 =
 // 0: a mesh without a distance field.
 template <int N1>
-__global__ __launch_bounds__(256) void k_select(LocArgs a, const double *__restrict__ basis,
+__global__ __launch_bounds__(256) void k_select(LocArgs a, StatArgs q,
+                                                const double *__restrict__ basis,
                                                 int *__restrict__ code,
                                                 int *__restrict__ el, double *__restrict__ rst,
                                                 double *__restrict__ dist2)
 {
     if (a.only && !*a.gate) return;
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (blockIdx.x < kStatsBlocks) {
+        fold_stats(a, q);
+        return;
+    }
+    const int t = (blockIdx.x - kStatsBlocks) * blockDim.x + threadIdx.x;
     const bool on = task_on(a, t);
     if constexpr (N1 > 0) {
         const int n = on ? a.ncand[t] & kCountMask : 0;
@@ -835,10 +848,11 @@ constexpr int kBinary64Only = 6;
     return hipGetLastError();
 }
 
-static hipError_t launch_select(const fp_handle *h, const LocArgs &a, int pb, int *code, int *el,
-                                double *rst, double *dist2, hipStream_t s)
+static hipError_t launch_select(const fp_handle *h, const LocArgs &a, const StatArgs &q, int pb,
+                                int *code, int *el, double *rst, double *dist2, hipStream_t s)
 {
-#define FP_SELECT(N1) k_select<N1><<<pb, 256, 0, s>>>(a, h->d_basis, code, el, rst, dist2)
+#define FP_SELECT(N1) \
+    k_select<N1><<<kStatsBlocks + pb, 256, 0, s>>>(a, q, h->d_basis, code, el, rst, dist2)
     if (!a.res_dl) {
         FP_SELECT(0);
         return hipGetLastError();
@@ -950,17 +964,14 @@ int run_findpts(fp_handle *h, const Work &w, int npts, const double *pts, const 
         int nblk = 0;
         FP_HIP(launch_locate_kernel(h, a, n, K, s, &nblk));
         if (timed) FP_HIP(hipEventRecord(l1, s));
-        FP_HIP(launch_select(h, a, pb, co, eo, ro, dO, s));
-        k_stats<<<kStatsBlocks, 1024, 0, s>>>(w.cand_part, pb, w.iter_part, nblk, h->E,
-                                              w.elem_off, n, 1, nullptr, h->stats);
-        FP_HIP(hipGetLastError());
+        FP_HIP(launch_select(h, a, StatArgs{w.cand_part, w.iter_part, pb, nblk, n, h->stats}, pb,
+                             co, eo, ro, dO, s));
         // second pass over the flagged tasks with the axis-aligned candidates
         // only (other tasks get no candidates and keep their result)
         a.first = a.few = false;
         a.redo = nullptr;
         a.only = w.redo;
         a.pair_max = kPairMax;
-        FP_HIP(fill_int_gated(w.elem_cnt, 0, (long long)h->E + 1, w.gate, s));
         k_cand<<<pb, 256, 0, s>>>(a);
         FP_HIP(hipGetLastError());
         FP_HIP(scan_units(w.elem_cnt, w.elem_off, w.units, h->E, K, w.scan_tmp, s, w.gate));
@@ -977,10 +988,8 @@ int run_findpts(fp_handle *h, const Work &w, int npts, const double *pts, const 
             FP_HIP(hipEventRecord(m1, s));
             record(h, 4, m0, m1);
         }
-        FP_HIP(launch_select(h, a, pb, co, eo, ro, dO, s));
-        k_stats<<<kStatsBlocks, 1024, 0, s>>>(w.cand_part, 0, w.iter_part, nblk, h->E,
-                                              w.elem_off, 0, 0, w.gate, h->stats);
-        FP_HIP(hipGetLastError());
+        FP_HIP(launch_select(h, a, StatArgs{w.cand_part, w.iter_part, 0, nblk, 0, h->stats}, pb,
+                             co, eo, ro, dO, s));
         if (timed) {
             FP_HIP(hipEventRecord(t1, s));
             record(h, 0, l0, l1);

@@ -312,9 +312,8 @@ hipError_t count_few(const int *code, const int *el, int *pos, int *cnt, int n, 
     return hipGetLastError();
 }
 
-__global__ void k_fill_int(int *__restrict__ p, int v, long long n, const int *__restrict__ gate)
+__global__ void k_fill_int(int *__restrict__ p, int v, long long n)
 {
-    if (gate && !*gate) return;
     long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     long long stride = (long long)gridDim.x * blockDim.x;
     for (; i < n; i += stride) p[i] = v;
@@ -325,16 +324,7 @@ hipError_t fill_int(int *p, int value, long long n, hipStream_t s)
     if (n <= 0) return hipSuccess;
     long long blocks = (n + 255) / 256;
     if (blocks > 8192) blocks = 8192;
-    k_fill_int<<<(int)blocks, 256, 0, s>>>(p, value, n, nullptr);
-    return hipGetLastError();
-}
-
-hipError_t fill_int_gated(int *p, int value, long long n, const int *gate, hipStream_t s)
-{
-    if (n <= 0) return hipSuccess;
-    long long blocks = (n + 255) / 256;
-    if (blocks > 8192) blocks = 8192;
-    k_fill_int<<<(int)blocks, 256, 0, s>>>(p, value, n, gate);
+    k_fill_int<<<(int)blocks, 256, 0, s>>>(p, value, n);
     return hipGetLastError();
 }
 
