@@ -13,14 +13,16 @@
 //   k2_cand     per point: cell, box and session test (and the oriented box
 //               in the first round), candidate list and each pair's rank in
 //               its element
-//   scan        pair counts per element -> offsets; k2_scatter groups pairs
+//   scan        pair counts per element -> offsets and work units; k2_scatter
+//               groups pairs
 //   k2_locate   one wavefront per work unit (up to 64 pairs of one element):
 //               closest mapped node (node rows by scalar loads), trust-region
 //               Newton on [-1,1]^2 with the 3D rules
 //   k2_select   inside / border / not found, smallest inside id, distance
 //               discriminator across sessions
 // findpts2_eval groups points by element the same way (k2_eval, one
-// wavefront per work unit, field rows by scalar loads).
+// wavefront per work unit, field rows by scalar loads).  Small calls take 16
+// lanes per point in one kernel (k2_point, k2_eval_point).
 #include <algorithm>
 #include <cmath>
 #include <string>

@@ -9,7 +9,7 @@
 // Pipeline per pass of at most max_points points, all on the caller's stream:
 //   k_cand     per point: hash cell, box + session test, candidate list
 //              (ascending element ids) and each pair's rank in its element
-//   scan       pair counts per element -> element offsets
+//   scan       pair counts per element -> element offsets and work units
 //   k_scatter  pair slots grouped by element
 //   k_locate_mfma  (orders 1..7) one wavefront per work unit (a run of one
 //              element's pairs), element block in LDS, map and Jacobian of 16
@@ -17,6 +17,7 @@
 //   k_newton_pl  (orders 8..15) blocks of wavefronts per work unit, the element
 //              in LDS, matrix cores (fp_newton_pl.inc)
 //   k_select   per point: classification and owner rule, caller's order
+// Small calls take k_point instead, one wavefront per point (fp_point.inc).
 #include <algorithm>
 #include <cmath>
 
