@@ -120,7 +120,9 @@ struct WaveBasis {
     }
 
     // The lane's part of Sum_ijk F_ijk h_i h_j h_k at the basis' point (F: the
-    // element's nodes); the sum over the lanes is the value.
+    // element's nodes); the sum over the lanes is the value.  A lane past the
+    // last row loads row 0, and its sum is dropped by a select: a field may hold
+    // any value, and a weight of 0 would make NaN of an infinite one.
     __device__ __forceinline__ double field_part(const double *__restrict__ F) const
     {
         double v = 0.0;
@@ -133,7 +135,7 @@ struct WaveBasis {
             double s = 0.0;
 #pragma unroll
             for (int i = 0; i < N1; ++i) s = fma(Fr[i], sh[i].x, s);
-            v = fma(w, s, v);
+            v = fma(w, in ? s : 0.0, v);
         }
         return v;
     }
