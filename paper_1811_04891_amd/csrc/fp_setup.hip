@@ -168,15 +168,20 @@ __device__ __forceinline__ void block_reduce(double (&v)[NV], int nsum, double *
 // per element, one thread per node line): the packed copy, the axis-aligned
 // box, h_e, and the oriented box, with non-finite coordinates flagged.
 //
+// The coefficients are those of the coordinates relative to the element's middle
+// node: the transform's rounding then scales with h_e.  The boxes of absolute
+// coordinates fell short by 1.5e-6 h_e at order 12 and max|x| = 1e7 h_e, of
+// relative ones by 3e-13 (replayed against long double).
+//
 // Axis-aligned box: min and max of the Bernstein coefficients of each
 // coordinate (the inverse nodal-Bernstein matrix applied along r, s, t), with
 // the margin 1e-8 h_e + 1e-14 max|x|.
 // Oriented box: the frame Q is the Gram-Schmidt basis of the mean edge vectors
 // along r, s, t (identity if they are degenerate).  The rotated coordinates
 // u = Q (x - centre) are linear in x and the transform keeps constants, so
-// their Bernstein coefficients are Q (b - centre) of the coordinates' own; any
-// Q (orthonormal or not) keeps the bound rigorous.  Margin: the axis-aligned
-// box's, or tol h_e if larger.  The record is binary32 (Q and the centre are
+// their Bernstein coefficients are Q (b - centre) of the coordinates' own, for
+// any Q (orthonormal or not).  Margin: the axis-aligned box's, or tol h_e if
+// larger, so that the bound holds after rounding too.  The record is binary32 (Q and the centre are
 // rounded first, the bounds are computed for the rounded frame, then rounded
 // outward) and shares a 128-byte line with the axis-aligned box.
 //
@@ -229,9 +234,12 @@ __global__ __launch_bounds__(ElemShape<N1>::W *kWave) void k_elem(
 #pragma unroll
     for (int q = 0; q < 28; ++q) v[q] = q < 12 ? 0.0 : INFINITY;
     int flag = 0;
+    constexpr int mid = (N1 / 2) * (1 + N1 + N1 * N1);
+    double org[3];  // the middle node
 #pragma unroll
     for (int c = 0; c < 3; ++c) {  // lines along r: (j, k) = (c0, c1)
-        const double *src = (c == 0 ? x : (c == 1 ? y : z)) + e * V + row * N1;
+        const double *X = (c == 0 ? x : (c == 1 ? y : z)) + e * V, *src = X + row * N1;
+        org[c] = X[mid];
         double *dst = geom + (e * 3 + c) * V + row * N1;
         double a[N1], o[N1];
 #pragma unroll
@@ -242,7 +250,7 @@ __global__ __launch_bounds__(ElemShape<N1>::W *kWave) void k_elem(
             for (int i = 0; i < N1; ++i) {
                 dst[i] = a[i];
                 flag |= !isfinite(a[i]);
-                rs += a[i];
+                rs += a[i] - org[c];
                 v[12 + c] = fmin(v[12 + c], a[i]);
                 v[15 + c] = fmin(v[15 + c], -a[i]);
                 v[24] = fmin(v[24], -fabs(a[i]));
@@ -251,6 +259,8 @@ __global__ __launch_bounds__(ElemShape<N1>::W *kWave) void k_elem(
             v[3 + c] = (c0 == N1 - 1 ? rs : 0.0) - (c0 == 0 ? rs : 0.0);
             v[6 + c] = (c1 == N1 - 1 ? rs : 0.0) - (c1 == 0 ? rs : 0.0);
         }
+#pragma unroll
+        for (int i = 0; i < N1; ++i) a[i] -= org[c];
         bernstein_line<N1>(Bi, a, o);
         if (act) {
 #pragma unroll
@@ -294,8 +304,8 @@ __global__ __launch_bounds__(ElemShape<N1>::W *kWave) void k_elem(
     double bb[6], ctr[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        bb[2 * c] = v[18 + c] - m;
-        bb[2 * c + 1] = -v[21 + c] + m;
+        bb[2 * c] = org[c] + v[18 + c] - m;
+        bb[2 * c + 1] = org[c] - v[21 + c] + m;
         ctr[c] = (double)(float)(0.5 * (bb[2 * c] + bb[2 * c + 1]));
     }
     double Q[3][3];
@@ -325,7 +335,8 @@ __global__ __launch_bounds__(ElemShape<N1>::W *kWave) void k_elem(
     for (int q = 0; q < 8; ++q) u[q] = INFINITY;
 #pragma unroll
     for (int k = 0; k < N1; ++k) {
-        const double d0 = b[0][k] - ctr[0], d1 = b[1][k] - ctr[1], d2 = b[2][k] - ctr[2];
+        const double d0 = b[0][k] - (ctr[0] - org[0]), d1 = b[1][k] - (ctr[1] - org[1]),
+                     d2 = b[2][k] - (ctr[2] - org[2]);
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             const double w = Q[a][0] * d0 + Q[a][1] * d1 + Q[a][2] * d2;
