@@ -101,9 +101,10 @@ struct Work {
     int *res_in = nullptr;    // M x MC: inside flag
     int *redo = nullptr;      // M: second-pass flag per point
     int *gate = nullptr;      // 1: nonzero when the first pass flagged any point
-    int *scan_tmp = nullptr;  // block sums of the device scans
     unsigned *cand_part = nullptr;  // ceil(M / 256): per-block candidate counts
-    unsigned *iter_part = nullptr;  // unit_grid(E, M, kUnitMin): Newton iterations per block
+    int *scan_tmp = nullptr;  // tile sums of the scans (iter_part included)
+    unsigned *iter_part = nullptr;  // E + unit_spare(M, kUnitMin): Newton iterations per block
+    // in other arrays' room (lay_out)
     UnitRec *units = nullptr;     // unit list of the pairs
     UnitRec *ev_units = nullptr;  // unit list of the points
     unsigned *pt_part = nullptr;  // min(M, kPointMax) x kPointCounters (small calls)
@@ -238,6 +239,15 @@ inline int unit_limit(int E, int n, int most, int step)
     return k < least ? least : (k < most ? k : most);
 }
 
+// Smallest unit of the pairs of a workspace with MC candidate slots per point: kUnitMin,
+// more where the cell lists are longer, so that the pieces of crowded elements are at
+// most one per point (the room for the list, work_carve).
+inline int pair_unit_min(int MC)
+{
+    const int k = (MC + 15) / 16 * 16;
+    return k > kUnitMin ? k : kUnitMin;
+}
+
 // Records of a list of at most n entries of E elements at unit size K or more.
 inline size_t unit_records(long long E, long long n, int K)
 {
@@ -269,11 +279,14 @@ struct UnitList {
 // that can have entries, and up to 2 n / K (at most kUnitSpare) for the pieces of
 // crowded ones.  Units beyond the grid are taken by the grid-stride walk.
 constexpr long long kUnitSpare = 4096;
+inline long long unit_spare(long long n, int K)
+{
+    const long long extra = 2 * ((n + K - 1) / K);
+    return extra < kUnitSpare ? extra : kUnitSpare;
+}
 inline int unit_grid(int E, long long n, int K)
 {
-    long long extra = 2 * ((n + K - 1) / K);
-    if (extra > kUnitSpare) extra = kUnitSpare;
-    const long long g = (E < 2 * n ? (long long)E : 2 * n) + extra;
+    const long long g = (E < 2 * n ? (long long)E : 2 * n) + unit_spare(n, K);
     return (int)(g < 1 ? 1 : (g > 0x7fffffffLL ? 0x7fffffffLL : g));
 }
 

@@ -950,7 +950,7 @@ int run_findpts(fp_handle *h, const Work &w, int npts, const double *pts, const 
             }
             continue;
         }
-        const int K = unit_pairs(h, n);
+        const int K = std::max(unit_pairs(h, n), pair_unit_min(w.MC));
         a.few = h->E <= kFewMax && n / kFewPoints >= h->E;
         FP_HIP(fill_int(w.elem_cnt, 0, (long long)h->E + 1, s));
         k_cand<<<pb, 256, 0, s>>>(a);

@@ -25,7 +25,7 @@ using Clock = std::chrono::steady_clock;
 
 constexpr int kMaxSlots = 16;
 constexpr int kMaxPass = 1 << 20;  // points per findpts pass of a request
-constexpr int kMinPass = 32;       // points per pass of a request that just fits the budget
+constexpr int kMinPass = 256;
 constexpr int kMaxBypass = 8;      // later requests admitted past a waiting one
 constexpr size_t kWindow = 64;     // queued requests examined per admission
 

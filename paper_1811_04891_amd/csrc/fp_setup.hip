@@ -527,6 +527,19 @@ struct Layout {
     }
 };
 
+// A serving budget admits a request by these bytes, so what one of the two calls
+// needs only for itself lies in arrays that only the other one uses, or that are
+// dead at that time, and adds none:
+//   units     in ev_cnt .. ev_slot, 8 (E + 1) + 12 M bytes in a row.  At most
+//             min(E, M MC) + M MC / K + 2 records of 8 bytes with K >= pair_unit_min(MC),
+//             so M MC / K <= M.
+//   ev_units  in cand_pos .. order, 8 M MC + 8 (E + 1) bytes.  At most
+//             min(E, M) + M / kUnitMin + 2 records.
+//   pt_part   in res_in .. ev_slot, more than 20 M bytes; a small call uses none of
+//             these.  5 counters of 4 bytes for at most M wavefronts.
+//   scan_tmp  runs on into iter_part, E ints and more, which the Newton kernels write
+//             after the scans and k_select reads before the next ones; the tile sums
+//             take (E + 1023) / 1024 x 8 bytes or less.
 void lay_out(Layout &L, Work &w, int E, int MC, int M, bool delta)
 {
     const size_t m = (size_t)M, mc = (size_t)MC, e1 = (size_t)E + 1;
@@ -544,18 +557,18 @@ void lay_out(Layout &L, Work &w, int E, int MC, int M, bool delta)
     w.res_in = L.take<int>(m * mc);
     w.redo = L.take<int>(m);
     w.gate = L.take<int>(1);
-    w.scan_tmp = L.take<int>((size_t)scan_tmp_size((long long)E + 1));
     w.cand_part = L.take<unsigned>((m + 255) / 256);
-    w.units = L.take<UnitRec>(unit_records(E, (long long)(m * mc), kUnitMin));
-    w.ev_units = L.take<UnitRec>(unit_records(E, M, kUnitMin));
-    w.iter_part = L.take<unsigned>((size_t)unit_grid(E, M, kUnitMin));
-    w.pt_part = L.take<unsigned>((size_t)std::min(M, kPointMax) * kPointCounters);
+    w.scan_tmp = L.take<int>((e1 + 4095) / 4096 + 1);
+    w.iter_part = L.take<unsigned>((size_t)E + (size_t)unit_spare(M, kUnitMin));
     w.ev_cnt = L.take<int>(e1);
     w.ev_off = L.take<int>(e1);
     w.ev_pos = L.take<int>(m);
     w.ev_order = L.take<int>(m);
     w.ev_slot = L.take<int>(m);
     w.ev_sink = L.take<double>(kEvSink);
+    w.units = (UnitRec *)w.ev_cnt;
+    w.ev_units = (UnitRec *)w.cand_pos;
+    w.pt_part = (unsigned *)w.res_in;
 }
 }  // namespace
 
