@@ -679,9 +679,9 @@ int scratch_ptr(int dev, char **p)
 
 // Eval-only workspace carved from the scratch array: counters and offsets
 // of E + 1 elements and the scan's block sums, then the unit list and two
-// arrays of M points per pass, M as large as the array allows.  Returns false when E leaves no
-// room for a pass of kScratchMinPass points.
-constexpr int kScratchMinPass = 128;
+// arrays of M points per pass, M as large as the array allows (256 at the largest E).
+// Returns false for more elements than that.
+constexpr int kScratchMaxE = 4192191;
 
 static size_t round256(size_t b) { return (b + 255) / 256 * 256; }
 
@@ -691,7 +691,7 @@ static bool scratch_carve(char *base, int E, int npts, Work &w)
     const size_t fixed = 2 * round256(e1 * sizeof(int)) +
                          round256((size_t)scan_tmp_size((long long)E + 1) * sizeof(int)) +
                          round256(kEvSink * sizeof(double));
-    if (fixed >= kScratchBytes) return false;
+    if (E > kScratchMaxE) return false;
     // points per pass: the largest number, in steps of 64, whose arrays fit
     const size_t room = kScratchBytes - fixed;
     const auto arrays = [E](size_t m) {
@@ -701,7 +701,6 @@ static bool scratch_carve(char *base, int E, int npts, Work &w)
     size_t per = 0;
     for (size_t step = (size_t)1 << 22; step >= 64; step /= 2)
         if (arrays(per + step) <= room) per += step;
-    if (per < (size_t)kScratchMinPass) return false;
     const int M = (int)std::min<size_t>(per, (size_t)std::max(npts, 1));
     char *q = base;
     w = Work{};

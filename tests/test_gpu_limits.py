@@ -1,5 +1,5 @@
 """Limits that callers size against: the smallest serving budget that admits a
-request."""
+request, and the largest mesh the allocation-free interpolation takes."""
 import numpy as np
 import pytest
 import torch
@@ -50,3 +50,34 @@ def test_smallest_budget_of_a_request(shape, delta):
     assert ei.value.code == fp.FP_ENOMEM
     srv.destroy()
     h.free()
+
+
+def test_elements_of_the_allocation_free_interpolation():
+    """4,192,191 elements are the most; one more is refused.  The pass is then 256
+    points, and these go in 67."""
+    from paper_1811_04891_amd import findpts as fp
+    print("case: 4,192,191 and 4,192,192 elements", flush=True)
+    dev = torch.device("cuda:0")
+    m = w.box_mesh(64, 65503, 1, (0.0, 0.0, 0.0), (64.0, 65503.0, 1.0), N=1, device=dev)
+    n = 17000
+    g = torch.Generator(device=dev).manual_seed(2)
+    for E in (4192192, 4192191):
+        x, y, z = (c.reshape(-1, 8)[:E].contiguous() for c in (m.x, m.y, m.z))
+        h = fp.findpts_setup(x, y, z, 1, max_points=64)
+        el = torch.randint(0, E, (n,), generator=g, device=dev, dtype=torch.int32)
+        el[0] = E - 1
+        code = torch.zeros(n, dtype=torch.int32, device=dev)
+        rst = 2.0 * torch.rand((n, 3), generator=g, device=dev, dtype=torch.float64) - 1.0
+        out = torch.empty((1, n), dtype=torch.float64, device=dev)
+        if E > 4192191:
+            with pytest.raises(fp.FindptsError) as ei:
+                fp.findpts_eval_noalloc(h, code, el, rst, [y], out)
+            assert ei.value.code == fp.FP_ERANGE
+        else:
+            fp.findpts_eval_noalloc(h, code, el, rst, [y], out)
+            lo = y[el.long(), 0]
+            hi = y[el.long(), 7]
+            want = lo + (hi - lo) * 0.5 * (1.0 + rst[:, 1])
+            # sums of eight terms at the coordinate's magnitude
+            assert torch.max(torch.abs(out[0] - want)) <= 16 * 2.0 ** -53 * 65503.0
+        h.free()
