@@ -203,6 +203,7 @@ template <int N1>
 __device__ __forceinline__ void bernstein_line(cptr<double> Bi, const double (&v)[N1],
                                                double (&o)[N1])
 {
+    if constexpr (N1 <= 13) FP_PIN_SGPR(Bi);  // read per line: kept from one to the next it spills
 #pragma unroll
     for (int i = 0; i < N1; ++i) {
         double s = 0.0;
