@@ -543,7 +543,7 @@ int run_eval(fp_handle *h, const Work &w, int npts, const int *code, const int *
              const double *rst, int nfields, const double *const *h_fields, double *out,
              hipStream_t s, bool timed)
 {
-    const bool small = small_eval(h, npts);
+    const bool small = small_eval(h, npts, nfields);
     const size_t res_bytes = w.res ? (size_t)w.M * w.MC * 4 * sizeof(double) : 0;
     for (int start = 0; start < npts; start += w.M) {
         const int n = (npts - start < w.M) ? npts - start : w.M;

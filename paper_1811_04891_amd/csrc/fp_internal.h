@@ -391,9 +391,21 @@ inline bool small_call(const fp_handle *h, int npts)
 {
     return point_path(h) && npts <= (h->n1 <= 13 ? kPointMax : 6144);
 }
-inline bool small_eval(const fp_handle *h, int npts)
+// A point's wavefront reads its element's nodes of every field, which grouped points
+// share.  At orders up to 9, where the limit in points is the largest, the grouping is
+// therefore taken once a call reads more than kEvalNodes node values, its elements
+// have points to share (more than 3 each) and its units fill the chip.  Per point /
+// grouped in us: order 7, 480 elements, 16,384 points of 4, 8 and 16 fields 25 / 29, 58 / 32
+// and 115 / 49, 12,000 of 8 fields 45 / 33, 6,000 of 8 26 / 32; order 9, 16,384 of 16 fields
+// 248 / 103; but 3,000 of 16 fields on 11,776 elements of order 8 49 / 119, 1,000 of 16
+// fields on one element of order 9 28 / 93.
+constexpr double kEvalNodes = 3e7;
+inline bool small_eval(const fp_handle *h, int npts, int nfields)
 {
-    return point_path(h) && npts <= (h->n1 <= 10 ? kPointMax : (h->n1 <= 13 ? 8192 : 4096));
+    if (!point_path(h)) return false;
+    if (h->n1 > 10) return npts <= (h->n1 <= 13 ? 8192 : 4096);
+    const bool share = npts / 3 > h->E && h->E + npts / kUnitMin > 560;
+    return npts <= kPointMax && !(share && (double)npts * nfields * h->V > kEvalNodes);
 }
 
 // findpts / findpts_eval on a given workspace and stream (the public calls
