@@ -571,15 +571,51 @@ __device__ __forceinline__ void fold_stats(const LocArgs &a, const StatArgs &q)
 
 // Distance field at a point's inside candidates, for the points whose inside
 // candidates belong to two or more sessions (the only ones whose owner it
-// decides): the wavefront takes such points (want) one after another, its
-// lanes sharing each interpolation, and the point's own thread stores the
-// values.  Every solved pair used to interpolate it in its Newton kernel, by
+// decides).  Up to order kDeltaThread each point's thread interpolates its own; above, the
+// wavefront takes such points (want) one after another, its lanes sharing each
+// interpolation, and the point's own thread stores the values.  A wavefront whose points
+// all want it goes through 64 chains that way, each as long as one interpolation by a
+// thread at low orders, whose few node rows leave the lanes idle: findpts of 60,000
+// points that all lie in two meshes of 4,896 elements each, wavefront / thread, order 1
+// 233 / 140 us, 3 312 / 213, 5 422 / 330, 7 454 / 417, and of 500,000 points 798 / 542,
+// 1112 / 929, 1591 / 1570, 1765 / 2105 (order 6 2166 / 2429).
+//  Every solved pair used to interpolate it in its Newton kernel, by
 // the four lanes of its slot through dependent loads from global memory: 57 %
 // of that kernel on two overlapping annuli with 1.2e6 points, 10 % of them in
 // both meshes.
+constexpr int kDeltaThread = 5;
+
 template <int N1>
-__device__ __forceinline__ void select_delta(const LocArgs &a, BasisPtr<double> B, int t, int n,
-                                             bool want)
+__device__ __forceinline__ void thread_delta(const LocArgs &a, BasisPtr<double> B, int t, int n)
+{
+    for (int q = 0; q < n; ++q) {
+        const long long s = (long long)q * a.M + t;
+        if (a.res_in[s] != 1) continue;
+        double hr[N1], hs[N1], ht[N1];
+        lagrange<N1>(B, a.res[4 * s], hr);
+        lagrange<N1>(B, a.res[4 * s + 1], hs);
+        lagrange<N1>(B, a.res[4 * s + 2], ht);
+        const double *F = a.delta + (long long)a.cand_el[s] * (N1 * N1 * N1);
+        double v = 0.0;
+#pragma unroll
+        for (int k = 0; k < N1; ++k) {
+            double cs = 0.0;
+#pragma unroll
+            for (int j = 0; j < N1; ++j) {
+                double r = 0.0;
+#pragma unroll
+                for (int i = 0; i < N1; ++i) r = fma(F[N1 * (j + N1 * k) + i], hr[i], r);
+                cs = fma(r, hs[j], cs);
+            }
+            v = fma(cs, ht[k], v);
+        }
+        a.res_dl[s] = v;
+    }
+}
+
+template <int N1>
+__device__ __forceinline__ void wave_delta(const LocArgs &a, BasisPtr<double> B, int t, int n,
+                                           bool want)
 {
     unsigned long long todo = __ballot(want);
     if (todo == 0ull) return;
@@ -631,7 +667,12 @@ __global__ __launch_bounds__(256) void k_select(LocArgs a, StatArgs q,
             two = two || (s0 >= 0 && sk != s0);
             s0 = sk;
         }
-        select_delta<N1>(a, BasisPtr<double>{as_const(basis)}, t, n, two);
+        const BasisPtr<double> B{as_const(basis)};
+        if constexpr (N1 - 1 <= kDeltaThread) {
+            if (two) thread_delta<N1>(a, B, t, n);
+        } else {
+            wave_delta<N1>(a, B, t, n, two);
+        }
     }
     if (!on) return;
     const int p = t;
