@@ -65,8 +65,10 @@ __global__ __launch_bounds__(kFluxThreads) void k_flux_partial(
 
 // gamma from the partial sums, by every block for itself (4 KB from its L2: a
 // launch between the two kernels for it made the eight corrections of an exchange
-// step 10 us slower, 300 -> 290 us), and the correction of the block's points.
-constexpr int kFluxApplyBlocks = 2048;
+// step 10 us slower, 300 -> 290 us), and the correction of the block's points.  1e7 and
+// 3e7 points take 248 and 725 us with 1024 blocks, 266 and 775 with 2048 to 8192; up
+// to 3e6 points the number does not matter.
+constexpr int kFluxApplyBlocks = 1024;
 __global__ __launch_bounds__(kFluxThreads) void k_flux_apply(int npts,
                                                              const double *__restrict__ n,
                                                              long long ldn,
