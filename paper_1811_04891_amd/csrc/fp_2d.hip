@@ -1263,7 +1263,7 @@ extern "C" int findpts2(fp2_handle *h, int npts, const double *pts, const int *p
         a.iter_part = h->iter_part;
         a.cand_part = h->cand_part;
         a.pt_part = h->pt_part;
-        if (npts <= kPoint2Max) {
+        if (small_call2(h->E, npts)) {
             a.obb = h->obb;
             FP_HIP(launch_point2(h, a, code + start, el + start, rs + 2 * (long long)start,
                                  dist2 + start, s));
