@@ -681,7 +681,9 @@ def run_legs(args, fp, w, dev, head, on, stream):
         f1 = [(m1.x ** 2 + m1.y * m1.z + m1.z ** 3).contiguous()]
         h1, s1, r1, _ = run_workload(fp, dev, m1, p1, f1, args.steps, args.warmup, 1 << 14,
                                      (fp.FP_PREC_FP64,))
+        # (a small call: its locate_kernel is lookup, Newton and selection in one kernel)
         legs["unit_cube_c1"] = {"workload": "64 perturbed hexes N=5, 10,000 points, 1 field",
+                                "locate_kernel_covers": "the whole call",
                                 "fp64": summarize(5, p1.shape[0], 1, r1[fp.FP_PREC_FP64])}
         h1.free()
 

@@ -173,6 +173,16 @@ FP_API int findpts_eval_noalloc(fp_handle *h, int npts, const int *code, const i
 FP_API int findpts_set_precision(fp_handle *h, int precision);
 
 /*
+ * Small calls.  findpts takes a call of at most 16,384 points (6,144 at orders
+ * 13 to 15) with one wavefront per point in one kernel, findpts_eval and
+ * findpts_eval_noalloc one of at most 16,384 points (8,192 at orders 10 to 12,
+ * 4,096 above; at orders up to 9 not if it reads more than 3e7 node values,
+ * points x fields x (N+1)^3, of elements with more than 3 points each).  Other
+ * calls are grouped by element.  A mixed-precision handle of order up to 7 always
+ * groups.  The call's points and fields decide, not the passes it is cut into, and
+ * the two agree to rounding.  findpts2 takes 16 lanes per point up to 65,536 points
+ * (40,000 on at most 4,096 elements), findpts2_eval up to 65,536.
+ *
  * findpts_stats -- cumulative counters since setup (or the last reset),
  * written to host memory (6 values): h_counts[0] = (point, element) pairs
  * solved by Newton, h_counts[1] = Newton iterations, h_counts[2] = points
@@ -181,8 +191,10 @@ FP_API int findpts_set_precision(fp_handle *h, int precision);
  * box also holds the point, then redoes points left without an inside
  * element with all of them), h_counts[4] and h_counts[5] = the pairs and
  * iterations of [0] and [1] that the first-pass Newton launches solved (the
- * rest belong to the second passes).  Synchronises the device.  reset != 0
- * zeroes them afterwards.
+ * rest belong to the second passes).  A small call without a distance field
+ * solves a point's candidates up to its first inside element, so its [0], [1],
+ * [4] and [5] may be smaller than a grouped call's; [2] and [3] are the same.
+ * Synchronises the device.  reset != 0 zeroes them afterwards.
  */
 FP_API int findpts_stats(fp_handle *h, long long *h_counts, int reset);
 
@@ -192,7 +204,9 @@ FP_API int findpts_stats(fp_handle *h, long long *h_counts, int reset);
  * h_ms[5] with the summed milliseconds and h_n[5] with the launch counts of
  * [0] the first-pass Newton (locate) kernel, [1] the interpolation kernel,
  * [2] whole findpts calls, [3] whole findpts_eval calls, [4] the
- * second-pass Newton kernel, then clears them.
+ * second-pass Newton kernel, then clears them.  A small call has no phases: its
+ * [0] is its whole kernel (lookup, Newton and selection) and the fold of its
+ * counters, and it adds nothing to [4].
  * findpts_timing_read synchronises the recorded events.
  */
 FP_API int findpts_timing(fp_handle *h, int enable);
@@ -333,9 +347,7 @@ FP_API int fp_extrapolate(long long n, int order, const double *const *h_hist, d
  *     stream completes; waiting requests are then admitted.
  *   - Results equal those of findpts + findpts_eval on the request alone
  *     (every point's result depends only on that point, the mesh, and
- *     whether the call is small: calls of at most 16,384 points, 4,096 to
- *     8,192 at orders above 9, run other kernels, whose results may differ
- *     by rounding).
+ *     whether the call is small, above).
  *   - Latency of a request = host time from fps_submit to the completion of
  *     its last kernel (a host callback on its stream).
  *

@@ -1,9 +1,7 @@
-// Device-side tensor-product Lagrange basis on GLL nodes and the
-// sum-factorised element map (geometry and Jacobian) for one lane.
-//
-// The element data pointers are wave-uniform (one element per wavefront), so
-// their loads compile to scalar loads and every multiply-add takes the node
-// value as a scalar operand; the lane-varying part is only the basis values.
+// Device-side Lagrange basis on GLL nodes for one lane, and the address spaces that
+// element data is read through: wave-uniform pointers to data that is not written
+// while a kernel runs compile to scalar loads (a multiply-add then takes the node
+// value as a scalar operand), staged elements to LDS reads.
 #pragma once
 
 #include "fp_internal.h"

@@ -332,7 +332,7 @@ __device__ __forceinline__ int wave_rank(int *cnt, int e, bool act)
 // 1e6 points 1201 -> 1187), findpts_eval counts so whenever there are more points
 // than elements.  Locate / interpolation of 3 fields, order 7, before -> after:
 // 64 elements, 100,000 points 475 -> 287 us / 188 -> 41; 512 elements, 600,000
-// points 1094 -> 906 / 287 -> 112.
+// points 1094 -> 906 / 203 -> 112 (staged before).
 constexpr int kFewMax = 4096;
 constexpr int kFewPoints = 64;
 // Ranks of the candidate pairs of n points in their elements, cnt counted up:
@@ -370,10 +370,10 @@ std::vector<double> bernstein_to_nodal_inverse(int N, const double *z);
 hipError_t fill_int(int *p, int value, long long n, hipStream_t s);
 
 // Calls taken one wavefront per point, in one kernel, instead of being grouped
-// by element (k_point, k_eval_point): decided by the call's size alone, so that
-// a call's results do not depend on how it is cut into passes.  The grouped
+// by element (k_point, k_eval_point): decided by the call's points and fields, so
+// that a call's results do not depend on how it is cut into passes.  The grouped
 // path costs a call of 1,000 points 92 to 238 us of findpts at orders 3 to 9
-// (about 20 launches and a chain of 16-slot rounds) against 30 to 52 us, and 250
+// (about 15 launches and a chain of 16-slot rounds) against 30 to 52 us, and 250
 // to 500 us at orders 12 and 15 against 83 to 232.  At 16,000 points on 125 or
 // 2,048 elements it takes 110 to 235 us against 91 to 134 at orders 3 to 7, 270
 // to 350 against 227 to 267 at orders 9 and 10, 443 to 566 against 496 to 547
